@@ -42,6 +42,8 @@ struct span_pool {
   PoolIndex* index = nullptr;
   void* dev = nullptr;
   bool owns_dev = false;
+  // the attention kernels of this pool: the bf16 MFMA ones, else on bf16 pools the
+  // split-precision one, else (fp32 pools) the generic one
   bool use_mfma = false;
   std::set<span_plan_t*> plans;
   std::vector<hipEvent_t> event_cache;  // reusable timing events
@@ -62,6 +64,8 @@ int max_parts(const std::vector<CombineTile>& c) {
   for (const CombineTile& t : c) m = std::max(m, static_cast<int>(t.n_parts));
   return m;
 }
+
+Tiling plan_tiling(const span_plan_t* pl);
 
 // The (m, l) half of a split-KV partial buffer, after its part_o_elems O elements.
 float* part_ml_of(const span_pool* p, float* part, size_t part_o_elems) {
@@ -144,6 +148,7 @@ struct span_plan_t {
   unsigned sched_next = 0;
   int bm = kGenericBM;
   bool mfma = false;
+  bool split = false;  // bf16 pool, not mfma
   bool committed = false;
   double host_plan_us = 0.0;    // hashing, lookup, allocation, work lists
   double host_upload_us = 0.0;  // device metadata allocation and copy enqueue
@@ -185,6 +190,12 @@ struct span_plan_t {
 };
 
 namespace {
+Tiling plan_tiling(const span_plan_t* pl) {
+  const span_pool_config& c = pl->pool->cfg;
+  if (pl->split) return tiling_split(pl->bm, c.num_kv_heads * split_chunks(c.num_q_heads / c.num_kv_heads));
+  return tiling_for(pl->mfma, pl->bm, c.num_q_heads, c.num_kv_heads);
+}
+
 // The plan whose device data occupy each device's scratch region (span_plan_static).
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -287,8 +298,10 @@ int spanq::plan_impl(span_pool* pool, const span_query* qs, int32_t nq, void* st
   pl->stream = static_cast<hipStream_t>(stream);
   const bool device = pool->cfg.device >= 0;
   pl->mfma = device && pool->use_mfma;
-  pl->bm = pl->mfma ? mfma_bm(pool->cfg.num_q_heads / pool->cfg.num_kv_heads) : kGenericBM;
-  Tiling t = tiling_for(pl->mfma, pl->bm, pool->cfg.num_q_heads, pool->cfg.num_kv_heads);
+  pl->split = device && !pl->mfma && pool->cfg.dtype == SPAN_BF16;
+  const int group = pool->cfg.num_q_heads / pool->cfg.num_kv_heads;
+  pl->bm = pl->mfma ? mfma_bm(group) : pl->split ? split_bm(group) : kGenericBM;
+  Tiling t = plan_tiling(pl);
   t.materialize = (pool->cfg.flags & SPAN_FLAG_MATERIALIZE) != 0;
   std::string msg;
   const auto t_plan0 = std::chrono::steady_clock::now();
@@ -325,7 +338,8 @@ int spanq::plan_impl(span_pool* pool, const span_query* qs, int32_t nq, void* st
     }
     pl->rope = pool->rope_tab;
     auto& hb = pl->host_meta;
-    size_t o_kv = put(hb, P.kv), o_kt = put(hb, P.kv_tiles), o_k3p = put(hb, P.k3_prefill),
+    // the generic kernel reads key lists page by page, the others in tile records
+    size_t o_kv = pl->mfma || pl->split ? 0 : put(hb, P.kv), o_kt = put(hb, P.kv_tiles), o_k3p = put(hb, P.k3_prefill),
            o_k3c = put(hb, P.k3_cross);
     size_t o_tp = put(hb, P.t_prefill), o_tc = put(hb, P.t_cross), o_cb = put(hb, P.combine),
            o_mv = put(hb, P.moves);
@@ -708,6 +722,8 @@ int span_prefill_fragments(span_plan_t* pl, int32_t layer, const void* q, const 
   const int nch = P.prefill_chunks.empty() ? 0 : static_cast<int>(P.prefill_chunks.size()) - 1;
   e = pl->mfma ? launch_prefill_mfma(g, pl->tp, nt, pl->kt, q, out, pl->rope, sched, P.prefill_chunks.data(),
                                      pl->xch, nch, &pl->prefill_queues, s)
+      : pl->split
+          ? launch_attn_split(g, pl->tp, nt, pl->kt, q, out, nullptr, nullptr, pl->rope, s)
                : launch_attn_generic(g, pl->tp, nt, pl->kv, q, out, nullptr, nullptr, pl->rope, s);
   if (e != hipSuccess) return hip_fail(e, "span_prefill_fragments: attention");
   tm.mark(2);
@@ -751,6 +767,8 @@ int span_cross_attend(span_plan_t* pl, int32_t layer, const void* q, const void*
     if (fused) w = CrossWrites{pl->k3c, k, v};
     e = launch_attn_mfma(g, pl->tc, nt - nf, pl->kt, q, out, po, pml, pl->rope, w, s);
     if (e == hipSuccess && nf > 0) e = launch_few_mfma(g, pl->tc + (nt - nf), nf, pl->kt, q, po, pml, pl->rope, s);
+  } else if (pl->split) {
+    e = launch_attn_split(g, pl->tc, nt, pl->kt, q, out, po, pml, pl->rope, s);
   } else {
     e = launch_attn_generic(g, pl->tc, nt, pl->kv, q, out, po, pml, pl->rope, s);
   }
@@ -796,7 +814,7 @@ int span_plan_decode(span_plan_t* pl, const int32_t* n_new, const int64_t* rows,
   std::vector<int32_t> n(n_new, n_new + nq);
   std::vector<int64_t> r(rows, rows + nq);
   span_pool* pool = pl->pool;
-  Tiling t = tiling_for(pl->mfma, pl->bm, pool->cfg.num_q_heads, pool->cfg.num_kv_heads);
+  Tiling t = plan_tiling(pl);
   t.materialize = (pool->cfg.flags & SPAN_FLAG_MATERIALIZE) != 0;
   std::string msg;
   int rc = pool->index->decode(&P, n, r, t, &msg);
@@ -820,7 +838,7 @@ int span_plan_decode(span_plan_t* pl, const int32_t* n_new, const int64_t* rows,
   const Plan::DecodeStep& d = P.dec;
   auto& hb = pl->dec_host;
   hb.clear();
-  const size_t o_w = put(hb, d.writes), o_kv = put(hb, d.kv), o_kt = put(hb, d.kv_tiles), o_t = put(hb, d.tiles),
+  const size_t o_w = put(hb, d.writes), o_kv = pl->mfma || pl->split ? 0 : put(hb, d.kv), o_kt = put(hb, d.kv_tiles), o_t = put(hb, d.tiles),
                o_cb = put(hb, d.combine);
   hb.resize((hb.size() + 255) & ~static_cast<size_t>(255));
   e = hipMallocAsync(reinterpret_cast<void**>(&pl->dec.meta), hb.size(), s);
@@ -874,6 +892,8 @@ int span_decode_attend(span_plan_t* pl, int32_t layer, const void* q, const void
     e = launch_attn_mfma(g, pl->dec.tiles, nt - nf, pl->dec.kt, q, out, po, pml, pl->dec.rope, CrossWrites{}, s);
     if (e == hipSuccess && nf > 0)
       e = launch_few_mfma(g, pl->dec.tiles + (nt - nf), nf, pl->dec.kt, q, po, pml, pl->dec.rope, s);
+  } else if (pl->split) {
+    e = launch_attn_split(g, pl->dec.tiles, nt, pl->dec.kt, q, out, po, pml, pl->dec.rope, s);
   } else {
     e = launch_attn_generic(g, pl->dec.tiles, nt, pl->dec.kv, q, out, po, pml, pl->dec.rope, s);
   }

@@ -41,8 +41,6 @@ namespace {
 
 using namespace mfma;
 
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
 constexpr int kFStages = 4;  // LDS ring depth; tiles are fetched in pairs, two ahead
 constexpr int kFG = 4;       // query heads per kv head (rows per item: at most 16)
 
@@ -72,20 +70,6 @@ __device__ __forceinline__ void wait_tiles_f(int k) {
     wait_vmcnt<NDMA>();
   else
     wait_vmcnt<0>();
-}
-
-// x combined with the values of lanes l ^ 16, l ^ 32 and l ^ 48 (the row's lanes)
-__device__ __forceinline__ float row_max4(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float row_sum4(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 }  // namespace

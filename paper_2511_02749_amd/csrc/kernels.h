@@ -30,11 +30,20 @@ hipError_t launch_append_kv(const PoolGeom& g, const SlotWrite* writes, int n_wr
 hipError_t launch_move_pages(const PoolGeom& g, const MovePage* moves, int n_moves, const float2* rope,
                              hipStream_t s);
 
-// Generic (vector ALU) span attention over work tiles of up to 64 rows.
+// Generic span attention (any dtype, any heads per kv head) over work tiles of up to
+// kGenericBM rows.
 constexpr int kGenericBM = 64;
 hipError_t launch_attn_generic(const PoolGeom& g, const WorkTile* tiles, int n_tiles, const KvPage* kv,
                                const void* q, void* out, void* part_o, float* part_ml,
                                const float2* rope, hipStream_t s);
+
+// bf16 pools at fp32 precision of queries and weights, any number g of query heads per
+// kv head: row tiles of up to split_bm(g) tokens, split_chunks(g) work items per tile and
+// kv head; key lists in tile records, as for the MFMA kernels below.
+int split_bm(int g);
+int split_chunks(int g);
+hipError_t launch_attn_split(const PoolGeom& g, const WorkTile* tiles, int n_tiles, const TileRec* kt, const void* q,
+                             void* out, void* part_o, float* part_ml, const float2* rope, hipStream_t s);
 
 // bf16 MFMA attention kernels: eight waves per work-group, work items (row tile,
 // kv head); a row tile has mfma_bm(g) = 256 / g query tokens (g = query heads per

@@ -1,4 +1,4 @@
-// Page writer (K3), generic span attention and KV-split combine for gfx950.
+// Page writer (K3), decode writes, page moves and KV-split combine for gfx950.
 //
 // Rotary encoding (section 5.5 cites RoFormer): rotate-half pairs (i, i + d/2)
 // at angle pos * theta^(-2i/d); cos/sin come from the pool's position table.
@@ -239,140 +239,6 @@ hipError_t launch_move_pages(const PoolGeom& g, const MovePage* moves, int n, co
   }
   if (g.d == 128) return move_pages_t<float, 128>(g, moves, n, rope, s);
   return move_pages_t<float, 64>(g, moves, n, rope, s);
-}
-
-// ------------------------------------------------------------------ generic attention
-// One wave per (tile, query head); lane r owns query row r of the tile.  Each
-// key page is staged in LDS (rotated by the page's delta when it is read from a
-// different position than it was written at), then every lane scores its row
-// against the 16 slots and folds them into an online softmax (base 2).
-template <typename T, int D>
-__global__ __launch_bounds__(64) void attn_generic_kernel(const WorkTile* __restrict__ tiles,
-                                                          const KvPage* __restrict__ kv,
-                                                          const T* __restrict__ q, T* __restrict__ out,
-                                                          const T* __restrict__ pool, int64_t layer_off, int hq,
-                                                          int hkv, float scale_log2,
-                                                          const float2* __restrict__ rope,
-                                                          void* __restrict__ part_o, float* __restrict__ part_ml) {
-  constexpr int H = D / 2;
-  __shared__ float ks[kPage][D + 1];
-  __shared__ float vs[D][kPage + 1];
-  const WorkTile t = tiles[blockIdx.x];
-  const int h = blockIdx.y;
-  const int g = (h * hkv) / hq;
-  const int lane = threadIdx.x;
-  const bool active = lane < t.n_rows;
-  const int qpos = t.q_pos0 + lane;
-  const int64_t page_elems = 2ll * hkv * kPage * D;
-
-  float qv[D];
-  float acc[D];
-#pragma unroll
-  for (int i = 0; i < D; ++i) acc[i] = 0.f;
-  if (active) {
-    const T* qr = q + (static_cast<int64_t>(t.q_row0 + lane) * hq + h) * D;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      float sn, cs;
-      rope_cs(rope, D / 2, qpos, i, &sn, &cs);
-      const float x0 = to_f32(qr[i]);
-      const float x1 = to_f32(qr[i + H]);
-      qv[i] = x0 * cs - x1 * sn;
-      qv[i + H] = x1 * cs + x0 * sn;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < D; ++i) qv[i] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  for (int pi = t.kv_begin; pi < t.kv_end; ++pi) {
-    const KvPage pg = kv[pi];
-    const T* kp = pool + layer_off + static_cast<int64_t>(pg.page_id) * page_elems + static_cast<int64_t>(g) * kPage * D;
-    const T* vp = pool + layer_off + static_cast<int64_t>(pg.page_id) * page_elems +
-                  static_cast<int64_t>(hkv) * kPage * D + static_cast<int64_t>(g) * D * kPage;
-    __syncthreads();
-    for (int e = lane; e < kPage * H; e += 64) {
-      const int s = e / H;
-      const int i = e - s * H;
-      float x0 = to_f32(kp[s * D + i]);
-      float x1 = to_f32(kp[s * D + i + H]);
-      if (pg.delta != 0) {
-        float sn, cs;
-        rope_cs(rope, D / 2, pg.delta, i, &sn, &cs);
-        const float y0 = x0 * cs - x1 * sn;
-        x1 = x1 * cs + x0 * sn;
-        x0 = y0;
-      }
-      ks[s][i] = x0;
-      ks[s][i + H] = x1;
-    }
-    for (int e = lane; e < D * kPage; e += 64) vs[e / kPage][e % kPage] = to_f32(vp[(e / kPage) * kPage + v_pos(e % kPage)]);
-    __syncthreads();
-    if (!active) continue;
-    float sc[kPage];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < kPage; ++s) {
-      const bool ok = s < pg.n_valid && pg.pos0 + s <= qpos;
-      float dot = 0.f;
-#pragma unroll
-      for (int i = 0; i < D; ++i) dot += qv[i] * ks[s][i];
-      sc[s] = ok ? dot * scale_log2 : -INFINITY;
-      mx = fmaxf(mx, sc[s]);
-    }
-    if (mx == -INFINITY) continue;
-    const float m_new = fmaxf(m, mx);
-    const float corr = exp2f(m - m_new);  // m == -inf gives 0
-    l *= corr;
-#pragma unroll
-    for (int i = 0; i < D; ++i) acc[i] *= corr;
-#pragma unroll
-    for (int s = 0; s < kPage; ++s) {
-      const float p = exp2f(sc[s] - m_new);
-      l += p;
-#pragma unroll
-      for (int i = 0; i < D; ++i) acc[i] += p * vs[i][s];
-    }
-    m = m_new;
-  }
-  if (!active) return;
-  const int64_t orow = static_cast<int64_t>(t.q_row0 + lane);
-  if (t.part < 0) {
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    T* o = out + (orow * hq + h) * D;
-#pragma unroll
-    for (int i = 0; i < D; ++i) o[i] = from_f32<T>(acc[i] * inv);
-  } else {
-    const int64_t slot = (static_cast<int64_t>(t.part) * hq + h) * kGenericBM + lane;
-    using P = typename PartOf<T>::type;
-    P* po = static_cast<P*>(part_o) + slot * D;
-    const float inv = !PartOf<T>::normalized ? 1.f : (l > 0.f ? 1.f / l : 0.f);
-#pragma unroll
-    for (int i = 0; i < D; ++i) po[i] = static_cast<P>(acc[i] * inv);
-    part_ml[slot * 2 + 0] = m;
-    part_ml[slot * 2 + 1] = l;
-  }
-}
-
-template <typename T, int D>
-static hipError_t attn_generic_t(const PoolGeom& g, const WorkTile* tiles, int n, const KvPage* kv, const void* q,
-                                 void* out, void* part_o, float* part_ml, const float2* rope, hipStream_t s) {
-  const float scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
-  hipLaunchKernelGGL((attn_generic_kernel<T, D>), dim3(n, g.hq), dim3(64), 0, s, tiles, kv,
-                     static_cast<const T*>(q), static_cast<T*>(out), static_cast<const T*>(g.base), g.layer_off,
-                     g.hq, g.hkv, scale_log2, rope, part_o, part_ml);
-  return hipGetLastError();
-}
-
-hipError_t launch_attn_generic(const PoolGeom& g, const WorkTile* tiles, int n, const KvPage* kv, const void* q,
-                               void* out, void* part_o, float* part_ml, const float2* rope, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  if (g.dtype == SPAN_BF16) {
-    if (g.d == 128) return attn_generic_t<bf16_t, 128>(g, tiles, n, kv, q, out, part_o, part_ml, rope, s);
-    return attn_generic_t<bf16_t, 64>(g, tiles, n, kv, q, out, part_o, part_ml, rope, s);
-  }
-  if (g.d == 128) return attn_generic_t<float, 128>(g, tiles, n, kv, q, out, part_o, part_ml, rope, s);
-  return attn_generic_t<float, 64>(g, tiles, n, kv, q, out, part_o, part_ml, rope, s);
 }
 
 // ------------------------------------------------------------------ K4 combine

@@ -635,7 +635,7 @@ int32_t list_end(const std::vector<KvPage>& kv, int32_t kv0, int32_t kv1, int32_
 }
 
 // Order of the prefill row tiles.
-// Generic kernel: longest key lists first, so the launch ends on short tiles.
+// Other kernels: longest key lists first, so the launch ends on short tiles.
 // MFMA kernel with 1, 2, 4 or 8 kv heads: queues for the chip's eight L2 domains
 // (XCDs).  The tiles are cut into R = 8 / kv_heads chunks; queue x serves chunk
 // x / kv_heads for kv head x mod kv_heads, so the work-groups of one XCD read the
@@ -649,7 +649,7 @@ void order_prefill(std::vector<WorkTile>& tiles, const std::vector<int32_t>& spa
   chunks->clear();
   auto work = [](const WorkTile& w) { return static_cast<int64_t>(w.kv_end - w.kv_begin); };
   const int hkv = t.kv_heads;
-  if (!t.pad4 || !(hkv == 1 || hkv == 2 || hkv == 4 || hkv == 8) || tiles.empty()) {
+  if (!t.xcd_queues || !(hkv == 1 || hkv == 2 || hkv == 4 || hkv == 8) || tiles.empty()) {
     std::stable_sort(tiles.begin(), tiles.end(),
                      [&](const WorkTile& a, const WorkTile& b) { return work(a) > work(b); });
     return;

@@ -61,7 +61,8 @@ struct Tiling {
   int kv_heads = 1;      // work items per tile (one per kv head)
   int target_items = 512;     // work-groups the cross launch aims for (KV splits x tiles x heads)
   int min_split_pages = 16;   // at least 256 keys per KV split
-  bool pad4 = false;          // pad span runs to 4-page tiles (MFMA kernel)
+  bool pad4 = false;          // pad span runs to 4-page tiles and emit tile records
+  bool xcd_queues = false;    // order prefill tiles for the per-XCD queues (MFMA prefill kernel)
   int two_group_rows = 0;     // cross tiles of at most this many rows use kTwoKeyGroups
   int few_rows = 0;           // two-key-group tiles of at most this many rows go last
                               // in the cross list (the 16-row kernel takes them)
@@ -72,8 +73,8 @@ struct Tiling {
 // Work-list shape for the attention kernels.  The MFMA kernel is persistent, one
 // 8-wave work-group per CU walking (row tile, kv head) items: the cross launch aims
 // at one item per CU (splitting the keys further only adds partials to merge).
-// The generic kernel (one wave per row tile and query head) is latency-bound and
-// wants more work-groups.
+// The generic kernel (fp32 pools: two work-groups of four waves per row tile and query
+// head) wants several work-groups per CU.
 // Few-row cross tiles (a short question over a long context) let the MFMA
 // kernel's two wave groups work on alternate key tiles; that needs four query
 // heads per kv head (two 32-row groups of four waves).
@@ -84,8 +85,21 @@ inline Tiling tiling_for(bool mfma, int bm, int hq, int hkv) {
   t.kv_heads = mfma ? hkv : hq;
   t.target_items = mfma ? 256 : 1024;
   t.pad4 = mfma;
+  t.xcd_queues = mfma;
   t.two_group_rows = (mfma && hq == 4 * hkv) ? 32 : 0;
   t.few_rows = t.two_group_rows > 0 ? 16 : 0;
+  return t;
+}
+
+// The split-precision kernel (bf16 pools outside the MFMA kernels' head counts, or on
+// request): items_per_tile work-groups per row tile, two of them on a CU at a time.
+inline Tiling tiling_split(int bm, int items_per_tile) {
+  Tiling t;
+  t.bm_prefill = bm;
+  t.bm_cross = bm;
+  t.kv_heads = items_per_tile;
+  t.target_items = 512;
+  t.pad4 = true;
   return t;
 }
 
