@@ -304,7 +304,7 @@ int prepare(span_model* m, int64_t T, int64_t R, const int32_t* h_rows, const in
       {&m->gu, Tz * 2 * F * bf}, {&m->act, Tz * F * bf}, {&m->q, Rz * hq * d * bf}, {&m->k, Rz * hkv * d * bf},
       {&m->v, Rz * hkv * d * bf}, {&m->o, Rz * hq * d * bf}, {&m->rows, Tz * 4 + 4}, {&m->toks, Tz * 4 + 4},
       {&m->last, static_cast<size_t>(nh) * 4 + 32}, {&m->nf, static_cast<size_t>(8) * H * bf},
-      {&m->part, static_cast<size_t>(lm_head_chunks(H)) * 8 * V * 4}, {&m->logits, static_cast<size_t>(8) * V * 4},
+      {&m->part, static_cast<size_t>(lm_head_chunks(H, V)) * 8 * V * 4}, {&m->logits, static_cast<size_t>(8) * V * 4},
       {&m->tok_out, 8 * 4}, {&m->best, argmax_scratch_bytes(8, V)},
       {&m->gemm.gemv_part, T <= 8 ? gemv_scratch(c, static_cast<int>(T)) : 0},
       {&m->gemm.sk_part, skinny_scratch(c, T)}};
@@ -409,25 +409,19 @@ int run_layers(span_model* m, int64_t T, int n_layers, int64_t base, hipStream_t
 }
 
 // Final RMSNorm, LM head and argmax of the nh compact rows listed in m->last, in
-// groups of up to 8 (a group padded to 1, 2, 4 or 8 rows repeats its last row).
+// groups of up to 8.
 // Logits to logits_out [nh][vocab] if given; tokens to *toks if given (waits).
 int lm_head(span_model* m, int nh, float* logits_out, std::vector<int32_t>* toks, hipStream_t s, const char* who) {
   const span_model_config& c = m->cfg;
   const int H = c.hidden, V = c.vocab;
-  const size_t bf = 2;
   if (toks) toks->assign(static_cast<size_t>(nh), -1);
   hipError_t e = hipSuccess;
   for (int g0 = 0; g0 < nh; g0 += 8) {
     const int ng = std::min(8, nh - g0);
-    const int np = ng <= 1 ? 1 : ng <= 2 ? 2 : ng <= 4 ? 4 : 8;
     e = launch_rmsnorm(m->x.p, m->last.as<int32_t>() + g0, c.final_norm, m->nf.p, ng, H, c.rms_eps, s);
-    for (int r = ng; e == hipSuccess && r < np; ++r)
-      e = hipMemcpyAsync(static_cast<char*>(m->nf.p) + static_cast<size_t>(r) * H * bf,
-                         static_cast<char*>(m->nf.p) + static_cast<size_t>(ng - 1) * H * bf, H * bf,
-                         hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = launch_lm_head(m->nf.p, c.lm_head, m->part.as<float>(), np, H, V, s);
+    if (e == hipSuccess) e = launch_lm_head(m->nf.p, c.lm_head, m->part.as<float>(), ng, H, V, s);
     float* lg = logits_out ? logits_out + static_cast<size_t>(g0) * V : nullptr;
-    if (e == hipSuccess) e = launch_argmax(m->part.as<float>(), np, ng, H, V, lg, m->tok_out.as<int32_t>(), m->best.p, s);
+    if (e == hipSuccess) e = launch_argmax(m->part.as<float>(), ng, ng, H, V, lg, m->tok_out.as<int32_t>(), m->best.p, s);
     if (e == hipSuccess && toks)
       e = hipMemcpyAsync(toks->data() + g0, m->tok_out.p, static_cast<size_t>(ng) * 4, hipMemcpyDeviceToHost, s);
     if (e != hipSuccess) return hip_err(e, std::string(who) + ": LM head");

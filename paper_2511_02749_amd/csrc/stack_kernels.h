@@ -65,12 +65,13 @@ hipError_t launch_reduce_residual_norm(const float* part, int slices, int M, int
 // out[c][r] = in[r][c] for an R x C bf16 matrix.
 hipError_t launch_transpose_bf16(const void* in, void* out, int64_t R, int64_t C, hipStream_t s);
 
-// LM head over nq (1, 2, 4 or 8) rows of nf [nq][hidden]: partial logits per chunk
-// of the hidden dimension into part [lm_head_chunks(hidden)][nq][vocab] (fp32).
+// LM head over nq (1 to 8) rows of nf [nq][hidden], the GEMV's first pass: partial
+// logits per slice of the hidden dimension into part [lm_head_chunks(hidden, vocab)]
+// [nq][vocab] (fp32).
 // launch_argmax sums the chunks (in chunk order) for the first n_rows rows into
 // logits [n_rows][vocab] (optional) and writes their argmax, lowest id on ties,
 // to token [n_rows]; scratch holds argmax_scratch_bytes(nq, vocab) of device memory.
-int lm_head_chunks(int hidden);
+int lm_head_chunks(int hidden, int vocab);
 hipError_t launch_lm_head(const void* nf, const void* w, float* part, int nq, int hidden, int vocab, hipStream_t s);
 size_t argmax_scratch_bytes(int nq, int vocab);
 hipError_t launch_argmax(const float* part, int nq, int n_rows, int hidden, int vocab, float* logits, int32_t* token,

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "stack_kernels.h"
 
@@ -138,54 +139,6 @@ __global__ void swiglu_kernel(const uint4* __restrict__ gu, uint4* __restrict__ 
   }
 }
 
-constexpr int kHeadThreads = 256;
-constexpr int kHeadCols = kHeadThreads * 8;  // vocab columns per work-group
-
-// Partial logits of nq rows over a chunk of the hidden dimension:
-// part[chunk][q][c] = sum over h in the chunk of n[q][h] * w[h][c].  Work-group
-// (column block, chunk); each thread owns 8 consecutive columns.
-template <int NQ>
-__global__ __launch_bounds__(kHeadThreads) void lm_head_kernel(const u16* __restrict__ n, const uint4* __restrict__ w,
-                                                               float* __restrict__ part, int hidden, int vocab,
-                                                               int chunk_rows) {
-  const int col0 = blockIdx.x * kHeadCols + threadIdx.x * 8;
-  const int h0 = blockIdx.y * chunk_rows;
-  const int h1 = min(hidden, h0 + chunk_rows);
-  float acc[NQ][8];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q)
-#pragma unroll
-    for (int t = 0; t < 8; ++t) acc[q][t] = 0.f;
-  if (col0 < vocab) {
-    const int vrow = vocab / 8;
-    auto row = [&](int h, const uint4& wv) {  // weight row h into the sums
-      float f[8];
-      unpack8(wv, f);
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const float a = bf(n[static_cast<int64_t>(q) * hidden + h]);
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc[q][t] = fmaf(a, f[t], acc[q][t]);
-      }
-    };
-    int h = h0;
-    for (; h + 8 <= h1; h += 8) {  // eight rows of weights in flight, then their sums in row order
-      uint4 wv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) wv[u] = w[static_cast<int64_t>(h + u) * vrow + col0 / 8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) row(h + u, wv[u]);
-    }
-    for (; h < h1; ++h) row(h, w[static_cast<int64_t>(h) * vrow + col0 / 8]);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      float* p = part + (static_cast<int64_t>(blockIdx.y) * NQ + q) * vocab + col0;
-      *reinterpret_cast<float4*>(p) = float4{acc[q][0], acc[q][1], acc[q][2], acc[q][3]};
-      *reinterpret_cast<float4*>(p + 4) = float4{acc[q][4], acc[q][5], acc[q][6], acc[q][7]};
-    }
-  }
-}
-
 // Logits = the chunks' partials summed in chunk order; token = argmax, lowest id on
 // ties, in two passes.  Pass 1, one work-group per (block of kArgCols columns, row):
 // the sums (stored as logits if asked) and the block's best value with its lowest
@@ -275,82 +228,113 @@ __global__ __launch_bounds__(kArgThreads) void argmax_rows_kernel(const float* _
   if (threadIdx.x == 0) token[q] = si[0];
 }
 
-// GEMV for a few rows (decode steps): Y[M][N] = X[M][K] W[K][N] (+ Y), M <= 8,
-// bf16 in and out, fp32 sums.  Pass 1, work-group (64 columns, one of kGemvChunks
-// slices of K): thread (row group g = 0..31, column lane) takes rows g, g + 32, ..
-// of the slice and 8 consecutive columns (a wave reads 8 whole 128-byte row
-// segments per load); the row groups meet in LDS and the work-group writes fp32
-// partials for its slice.  Pass 2, one thread per output element: the slices'
-// partials summed in slice order, the residual added, rounded once.  (A last
-// work-group per column block finishing the sum in pass 1 would need a device-scope
-// release per work-group; across this chip's eight L2s that costs more than the
-// second launch.)  Bound: HBM (W read once; partials of kGemvChunks x 4 bytes per
-// output element).
-constexpr int kGemvCols = 64;
-constexpr int kGemvChunks = 16;
+// GEMV for a few rows (decode steps, the LM head): Y[M][N] = X[M][K] W[K][N] (+ Y),
+// M <= 8, bf16 in and out, fp32 sums.  Pass 1, work-group (8 CL columns, one slice of K):
+// thread (row group, column lane of CL) takes every 256 / CL-th row of the slice and 8
+// consecutive columns, so a wave reads whole 128- or 256-byte row segments, eight loads
+// always in flight; the slice of X sits in LDS as fp32, [k][M], so that a weight row's M
+// factors are one or two 16-byte reads.  The row groups meet by lane swaps, then the
+// four waves in LDS, and the work-group writes fp32 partials for its slice.  Pass
+// 2, one thread per output element: the slices' partials summed in slice order, the
+// residual added, rounded once.  (A last work-group per column block finishing the sum in
+// pass 1 would need a device-scope release per work-group; across this chip's eight L2s
+// that costs more than the second launch.)
+//
+// Bound: HBM (W read once; slices x 4 bytes of partials per output element).  Against one
+// 2-byte load of X per weight row and M, and a reduction over 32 row groups in LDS, both
+// passes from the last-level cache, us before -> now at 4 rows: 2048 x 16384 22.3 -> 17,
+// 2048 x 32000 38.9 -> 29 (59 -> 29 as the LM head, whose work-groups of 2048 columns
+// filled half the chip), 8192 x 2048 13.1 -> 11.2, 2048 x 3072 7.6 -> 8.0; at 8 rows
+// 43 -> 23, 75.8 -> 36, 16.2 -> 15.7, 12.0 -> 9.6; at 1 row the same to 7%.
+// Slices (gemv_slices): about four work-groups per CU, but 128 to 512 rows of K each and
+// at most 16 unless that makes them longer: shorter ones spend their time in the
+// reduction, and pass 2, whose one work-group per row reads every slice, grows (64-row
+// slices: 8.0 -> 11.1 us at 2048 x 3072, 4 rows).
+// Column blocks: 128 columns read longer segments and reduce less, 64 give twice the
+// work-groups.  The line is two work-groups of 128 columns per CU: 8192 x 2048 (256) takes
+// 13.8 us with 128 columns and 11.2 with 64, 4096 x 4096 (512) 10.3 and 11.5.
+constexpr int kGemvMaxRows = 512;  // rows of K per slice
 
-template <int MP>
+template <int MP, int CL>
 __global__ __launch_bounds__(256) void gemv_partial_kernel(const u16* __restrict__ x, const uint4* __restrict__ w,
                                                            float* __restrict__ part, int M, int N, int K,
                                                            int rows_per_chunk) {
-  __shared__ float red[32][MP][kGemvCols];
-  const int cl = threadIdx.x & 7;
-  const int rg = threadIdx.x >> 3;
+  constexpr int U = 8;           // loads in flight
+  constexpr int kGemvCols = 8 * CL;
+  constexpr int RG = 256 / CL;   // row groups
+  __shared__ float xs[kGemvMaxRows * MP];
+  __shared__ float red[4][MP][kGemvCols];
+  const int cl = threadIdx.x % CL;
+  const int rg = threadIdx.x / CL;
   const int c0 = blockIdx.x * kGemvCols + cl * 8;
   const int k0 = blockIdx.y * rows_per_chunk;
-  const int k1 = min(K, k0 + rows_per_chunk);
+  const int n_k = min(K - k0, rows_per_chunk);  // at least 1
+  const int64_t vrow = N / 8;
+  const uint4* wp = w + static_cast<int64_t>(k0) * vrow + c0 / 8;
+  const bool cols = c0 < N;
+  uint4 wv[U];
+  auto fetch = [&](int u, int k) {  // row k of the slice
+    wv[u] = uint4{0u, 0u, 0u, 0u};
+    if (cols && k < n_k) wv[u] = wp[static_cast<int64_t>(k) * vrow];
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) fetch(u, rg + RG * u);
+  for (int k = threadIdx.x; k < n_k; k += 256) {
+#pragma unroll
+    for (int m = 0; m < MP; ++m) xs[k * MP + m] = m < M ? bf(x[static_cast<int64_t>(m) * K + k0 + k]) : 0.f;
+  }
+  __syncthreads();
   float acc[MP][8];
 #pragma unroll
   for (int m = 0; m < MP; ++m)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[m][j] = 0.f;
-  if (c0 < N) {
-    const int64_t vrow = N / 8;
-    int k = k0 + rg;
-    for (; k + 96 < k1; k += 128) {  // four rows in flight
-      uint4 wv[4];
+  for (int k = rg; k < n_k; k += RG * U) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) wv[u] = w[static_cast<int64_t>(k + 32 * u) * vrow + c0 / 8];
+    for (int u = 0; u < U; ++u) {
+      const int kk = k + RG * u;
+      float f[8], a[MP];
+      unpack8(wv[u], f);
+      fetch(u, kk + RG * U);  // its place is taken at once: U loads stay in flight
+      if (kk >= n_k) break;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        float f[8];
-        unpack8(wv[u], f);
+      for (int m = 0; m < MP; ++m) a[m] = xs[kk * MP + m];
 #pragma unroll
-        for (int m = 0; m < MP; ++m) {
-          if (m >= M) break;
-          const float a = bf(x[static_cast<int64_t>(m) * K + k + 32 * u]);
+      for (int m = 0; m < MP; ++m)
 #pragma unroll
-          for (int j = 0; j < 8; ++j) acc[m][j] = fmaf(a, f[j], acc[m][j]);
-        }
-      }
-    }
-    for (; k < k1; k += 32) {
-      float f[8];
-      unpack8(w[static_cast<int64_t>(k) * vrow + c0 / 8], f);
-#pragma unroll
-      for (int m = 0; m < MP; ++m) {
-        if (m >= M) break;
-        const float a = bf(x[static_cast<int64_t>(m) * K + k]);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[m][j] = fmaf(a, f[j], acc[m][j]);
-      }
+        for (int j = 0; j < 8; ++j) acc[m][j] = fmaf(a[m], f[j], acc[m][j]);
     }
   }
+  // The wave's four row groups (lanes 16 and 32 apart), four sums at a time: after a
+  // swap of halves and one of 16-lane rows, row h of a register holds the whole of sum
+  // {0, 2, 1, 3}[h].  Then the four waves, through LDS.
+  auto swap32 = [](float a, float b) {  // a in the low half, b in the high one, both halves summed
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+  };
+  auto swap16 = [](float a, float b) {
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+  };
+  const int h = (threadIdx.x >> 4) & 3;
+  const int jh = ((h & 1) << 1) | (h >> 1);
 #pragma unroll
   for (int m = 0; m < MP; ++m)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) red[rg][m][cl * 8 + j] = acc[m][j];
-  __syncthreads();
-  // thread t sums column t % 64 of rows t / 64, t / 64 + 4, .. over the row groups
-  const int col = threadIdx.x % kGemvCols;
-  const int n_t = blockIdx.x * kGemvCols + col;
-  if (n_t < N)
-    for (int m = threadIdx.x / kGemvCols; m < M; m += 256 / kGemvCols) {
-      float sum = 0.f;
-#pragma unroll 8
-      for (int g = 0; g < 32; ++g) sum += red[g][m][col];
-      part[(static_cast<int64_t>(blockIdx.y) * M + m) * N + n_t] = sum;
+    for (int j = 0; j < 8; j += 4) {
+      float t = swap16(swap32(acc[m][j], acc[m][j + 1]), swap32(acc[m][j + 2], acc[m][j + 3]));
+      if constexpr (CL == 8)  // eight row groups: lanes 8 apart too (a rotation by 8 in each row of 16)
+        t += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(t), 0x128, 0xf, 0xf, true));
+      if (CL == 16 || (threadIdx.x & 8) == 0) red[threadIdx.x >> 6][m][8 * cl + j + jh] = t;
     }
+  __syncthreads();
+  for (int i = threadIdx.x; i < M * kGemvCols; i += 256) {
+    const int m = i / kGemvCols, col = i % kGemvCols;
+    const int n_t = blockIdx.x * kGemvCols + col;
+    if (n_t < N)
+      part[(static_cast<int64_t>(blockIdx.y) * M + m) * N + n_t] =
+          (red[0][m][col] + red[1][m][col]) + (red[2][m][col] + red[3][m][col]);
+  }
 }
 
 __global__ __launch_bounds__(256) void gemv_reduce_kernel(const float* __restrict__ part, int chunks, int M, int N,
@@ -516,48 +500,57 @@ hipError_t launch_swiglu(const void* gu, void* act, int64_t n, int ffn, hipStrea
   return hipGetLastError();
 }
 
-int lm_head_chunks(int hidden) { return hidden >= 2048 ? 8 : 1; }
-
-hipError_t launch_lm_head(const void* nf, const void* w, float* part, int nq, int hidden, int vocab, hipStream_t s) {
-  const int chunks = lm_head_chunks(hidden);
-  const int rows = (hidden + chunks - 1) / chunks;
-  const dim3 grid((vocab + kHeadCols - 1) / kHeadCols, chunks);
-  const u16* n = static_cast<const u16*>(nf);
-  const uint4* wv = static_cast<const uint4*>(w);
-  switch (nq) {
-    case 1: lm_head_kernel<1><<<grid, kHeadThreads, 0, s>>>(n, wv, part, hidden, vocab, rows); break;
-    case 2: lm_head_kernel<2><<<grid, kHeadThreads, 0, s>>>(n, wv, part, hidden, vocab, rows); break;
-    case 4: lm_head_kernel<4><<<grid, kHeadThreads, 0, s>>>(n, wv, part, hidden, vocab, rows); break;
-    case 8: lm_head_kernel<8><<<grid, kHeadThreads, 0, s>>>(n, wv, part, hidden, vocab, rows); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-size_t gemv_part_bytes(int M, int N, int K) {
-  (void)K;
-  return static_cast<size_t>(kGemvChunks) * M * N * sizeof(float);
-}
-
 namespace {
+// K slices of the GEMV's first pass and rows per slice (a multiple of 16).
+int gemv_slices(int N, int K, int* rows) {
+  const int blocks = (N + 127) / 128;
+  int s = std::min({(1024 + blocks - 1) / blocks, std::max(1, K / 128), 16});
+  s = std::max(s, (K + kGemvMaxRows - 1) / kGemvMaxRows);
+  *rows = ((K + s - 1) / s + 15) / 16 * 16;
+  return (K + *rows - 1) / *rows;
+}
+
 // Pass 1 of the GEMV; returns the number of K slices (0 on a launch error).
 int gemv_pass1(const void* x, const void* w, int M, int N, int K, float* part, hipStream_t s) {
-  const int chunks = std::min(kGemvChunks, (K + 31) / 32);
-  const int rows = (K + chunks - 1) / chunks;
-  const dim3 grid((N + kGemvCols - 1) / kGemvCols, chunks);
+  int rows = 0;
+  const int slices = gemv_slices(N, K, &rows);
   const u16* xx = static_cast<const u16*>(x);
   const uint4* ww = static_cast<const uint4*>(w);
-  if (M == 1) gemv_partial_kernel<1><<<grid, 256, 0, s>>>(xx, ww, part, M, N, K, rows);
-  else if (M == 2) gemv_partial_kernel<2><<<grid, 256, 0, s>>>(xx, ww, part, M, N, K, rows);
-  else if (M <= 4) gemv_partial_kernel<4><<<grid, 256, 0, s>>>(xx, ww, part, M, N, K, rows);
-  else gemv_partial_kernel<8><<<grid, 256, 0, s>>>(xx, ww, part, M, N, K, rows);
-  return hipGetLastError() == hipSuccess ? chunks : 0;
+  auto go = [&](auto mp) {
+    constexpr int MP = decltype(mp)::value;
+    const int blocks = (N + 127) / 128;
+    if (blocks * slices >= 512) {
+      gemv_partial_kernel<MP, 16><<<dim3(blocks, slices), 256, 0, s>>>(xx, ww, part, M, N, K, rows);
+    } else {
+      gemv_partial_kernel<MP, 8><<<dim3((N + 63) / 64, slices), 256, 0, s>>>(xx, ww, part, M, N, K, rows);
+    }
+  };
+  if (M == 1) go(std::integral_constant<int, 1>{});
+  else if (M == 2) go(std::integral_constant<int, 2>{});
+  else if (M <= 4) go(std::integral_constant<int, 4>{});
+  else go(std::integral_constant<int, 8>{});
+  return hipGetLastError() == hipSuccess ? slices : 0;
 }
 
 bool gemv_args_ok(int M, int N, int K, size_t part_bytes) {
   return M >= 1 && M <= 8 && N % 8 == 0 && K >= 1 && gemv_part_bytes(M, N, K) <= part_bytes;
 }
 }  // namespace
+
+size_t gemv_part_bytes(int M, int N, int K) {
+  int rows = 0;
+  return static_cast<size_t>(gemv_slices(N, K, &rows)) * M * N * sizeof(float);
+}
+
+int lm_head_chunks(int hidden, int vocab) {
+  int rows = 0;
+  return gemv_slices(vocab, hidden, &rows);
+}
+
+hipError_t launch_lm_head(const void* nf, const void* w, float* part, int nq, int hidden, int vocab, hipStream_t s) {
+  if (nq < 1 || nq > 8 || vocab % 8 != 0) return hipErrorInvalidValue;
+  return gemv_pass1(nf, w, nq, vocab, hidden, part, s) ? hipSuccess : hipGetLastError();
+}
 
 hipError_t launch_gemv(const void* x, const void* w, void* y, int M, int N, int K, bool residual, float* part,
                        size_t part_bytes, hipStream_t s) {
@@ -621,7 +614,7 @@ hipError_t launch_argmax(const float* part, int nq, int n_rows, int hidden, int 
   const int nb = (vocab + kArgCols - 1) / kArgCols;
   float* bv = static_cast<float*>(scratch);
   int* bi = reinterpret_cast<int*>(bv + static_cast<size_t>(nq) * nb);
-  argmax_blocks_kernel<<<dim3(nb, n_rows), kArgThreads, 0, s>>>(part, lm_head_chunks(hidden), nq, vocab, logits, bv, bi);
+  argmax_blocks_kernel<<<dim3(nb, n_rows), kArgThreads, 0, s>>>(part, lm_head_chunks(hidden, vocab), nq, vocab, logits, bv, bi);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   argmax_rows_kernel<<<n_rows, kArgThreads, 0, s>>>(bv, bi, nb, token);

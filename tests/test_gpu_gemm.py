@@ -90,3 +90,12 @@ def test_skinny_gemm_rows_do_not_depend_on_row_count():
         assert spanq._lib.probe_gemm(x[:M].contiguous(), w, y)[0] == 2
         outs.append(y[:9].cpu())
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("N,K", [(8, 8), (64, 136), (72, 2048), (1032, 520), (2048, 1544), (4104, 4096), (65544, 264)])
+def test_gemv_tiles_and_slices(M, N, K):
+    """The GEMV at the edges of its column blocks (64 and 128 columns, the rule between
+    them), of its row groups (K not a multiple of 16 or of a slice) and of its slices of
+    K (one short slice to many)."""
+    assert _run(M, N, K, residual=True, seed=M + N + K) == 1
