@@ -116,6 +116,13 @@ __device__ __forceinline__ void block_sync() {
   __asm__ volatile("" ::: "memory");
 }
 
+// A barrier after LDS stores that other waves will read: s_barrier by itself does not wait
+// for them, and a wave on another SIMD may be served its read first.
+__device__ __forceinline__ void block_sync_stores() {
+  __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  block_sync();
+}
+
 // x combined with the values of lanes l ^ 16, l ^ 32 and l ^ 48 (the row's lanes)
 __device__ __forceinline__ float row_max4(float x) {
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);

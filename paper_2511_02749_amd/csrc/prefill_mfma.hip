@@ -706,7 +706,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       v.w *= scale_log2;
       rt4[i] = v;
     }
-    block_sync();
+    block_sync_stores();
   }
 
   int ck = 0, cv = 0;  // ring slots of the compute tile
@@ -783,7 +783,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // item k + 3, store the previous item's rows, rotate this item's query, fetch
     wait_vm_all();
     if (threadIdx.x == 0) sched_lds[kpar] = grabbed_item();
-    block_sync();
+    block_sync_stores();
     ec2 = __builtin_amdgcn_readfirstlane(sched_lds[kpar]);
     kpar ^= 1;
     grab(ec2);
