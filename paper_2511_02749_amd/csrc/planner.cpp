@@ -102,6 +102,7 @@ PoolIndex::PoolIndex(int64_t num_pages, int32_t page_size, int32_t hash_mode)
   gen_.assign(static_cast<size_t>(num_pages), 0u);
   page_tokens_.resize(static_cast<size_t>(num_pages) * page_size);
   index_.reserve(static_cast<size_t>(std::min<int64_t>(num_pages, 1 << 20)));
+  freed_.resize(num_pages);
   reset();
 }
 
@@ -235,9 +236,8 @@ bool PoolIndex::spec_equal(const Spec& a, const Spec& b) const {
 
 int32_t PoolIndex::pop_free() {
   if (!freed_.empty()) {
-    auto it = freed_.begin();
-    int32_t pid = *it;
-    freed_.erase(it);
+    const int32_t pid = freed_.lowest();
+    freed_.erase(pid);
     return pid;
   }
   return static_cast<int32_t>(watermark_++);
@@ -247,8 +247,8 @@ void PoolIndex::push_free(int32_t pid) {
   pages_[pid] = PageRec{};
   if (pid + 1 == watermark_) {
     --watermark_;
-    while (!freed_.empty() && *freed_.rbegin() + 1 == watermark_) {
-      freed_.erase(std::prev(freed_.end()));
+    while (watermark_ > 0 && freed_.contains(watermark_ - 1)) {
+      freed_.erase(watermark_ - 1);
       --watermark_;
     }
   } else {
@@ -470,7 +470,14 @@ int PoolIndex::plan(const std::vector<QueryIn>& qs, bool build, const Tiling& ti
   std::vector<MoveSrc> moves;
   std::vector<std::vector<int32_t>> move_of(walk.size());
   if (tiling.materialize && hash_mode_ != SPAN_HASH_STOCK) {
-    std::unordered_map<uint64_t, int32_t> seen;
+    // (page, shift) -> copy, open addressing at most half full; a copy's key is formed
+    // again from its record
+    size_t most = 0;
+    for (size_t qi = 0; qi < qs.size(); ++qi)
+      for (int wi : query_spans[qi]) most += walk[wi].entries.size();
+    size_t mask = 64;
+    while (mask < 2 * most) mask *= 2;
+    std::vector<int32_t> seen(mask--, -1);
     for (size_t qi = 0; qi < qs.size(); ++qi) {
       if (qs[qi].cross.n == 0) continue;
       const auto& ids = query_spans[qi];
@@ -483,12 +490,14 @@ int PoolIndex::plan(const std::vector<QueryIn>& qs, bool build, const Tiling& ti
             const Entry& e = w.entries[pg];
             const int64_t page = e.hit ? e.x : -1 - static_cast<int64_t>(e.x);
             const uint64_t key = (static_cast<uint64_t>(page) << 32) ^ static_cast<uint32_t>(shift);
-            auto it = seen.find(key);
-            if (it == seen.end()) {
-              it = seen.emplace(key, static_cast<int32_t>(moves.size())).first;
+            size_t at = static_cast<size_t>(mix64(key)) & mask;
+            while (seen[at] >= 0 && (moves[seen[at]].page != page || moves[seen[at]].delta != shift))
+              at = (at + 1) & mask;
+            if (seen[at] < 0) {
+              seen[at] = static_cast<int32_t>(moves.size());
               moves.push_back({page, shift, std::min(ps, w.in.n - static_cast<int32_t>(pg) * ps)});
             }
-            mv.push_back(it->second);
+            mv.push_back(seen[at]);
           }
         }
         shift += w.in.n;

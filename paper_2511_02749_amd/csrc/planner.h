@@ -103,6 +103,42 @@ inline Tiling tiling_split(int bm, int items_per_tile) {
   return t;
 }
 
+// A set of ids in [0, n) as a bitmap, with a bit per word over it: lowest member,
+// insertion and removal touch a word of each.
+class IdSet {
+ public:
+  void resize(int64_t n) {
+    words_.assign(static_cast<size_t>((n + 63) / 64), 0);
+    top_.assign((words_.size() + 63) / 64, 0);
+    size_ = 0;
+  }
+  bool empty() const { return size_ == 0; }
+  int64_t size() const { return size_; }
+  bool contains(int64_t i) const { return (words_[i >> 6] >> (i & 63)) & 1; }
+  void insert(int32_t i) {  // not a member yet
+    words_[i >> 6] |= uint64_t{1} << (i & 63);
+    top_[i >> 12] |= uint64_t{1} << ((i >> 6) & 63);
+    ++size_;
+  }
+  void erase(int64_t i) {  // a member
+    if ((words_[i >> 6] &= ~(uint64_t{1} << (i & 63))) == 0) top_[i >> 12] &= ~(uint64_t{1} << ((i >> 6) & 63));
+    --size_;
+  }
+  int32_t lowest() const {  // of a set that is not empty
+    size_t t = 0;
+    while (top_[t] == 0) ++t;
+    const size_t w = 64 * t + static_cast<size_t>(__builtin_ctzll(top_[t]));
+    return static_cast<int32_t>(64 * w + static_cast<size_t>(__builtin_ctzll(words_[w])));
+  }
+  void clear() {
+    if (size_ != 0) resize(64 * static_cast<int64_t>(words_.size()));
+  }
+
+ private:
+  std::vector<uint64_t> words_, top_;
+  int64_t size_ = 0;
+};
+
 class PoolIndex;
 
 struct Plan {
@@ -170,7 +206,7 @@ class PoolIndex {
   int64_t lookup(uint64_t h) const;  // page id or -1
 
   int64_t num_pages() const { return num_pages_; }
-  int64_t free_count() const { return static_cast<int64_t>(freed_.size()) + (num_pages_ - watermark_); }
+  int64_t free_count() const { return freed_.size() + (num_pages_ - watermark_); }
   int64_t cached_count() const { return static_cast<int64_t>(index_.size()); }
   int64_t evictable_count() const { return n_evictable_; }
   int64_t pinned_count() const;
@@ -237,7 +273,7 @@ class PoolIndex {
   std::vector<int32_t> page_tokens_;
   std::unordered_map<uint64_t, int32_t> index_;
   // Free page ids: every id >= watermark_, plus the ids in freed_ (all < watermark_).
-  std::set<int32_t> freed_;
+  IdSet freed_;
   int64_t watermark_ = 0;
   // Evictable pages (published, unpinned) in LRU order: a binary min-heap of
   // (last_use, -idx, id) entries with lazy deletion.  An entry is current iff its
