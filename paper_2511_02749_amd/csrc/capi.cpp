@@ -801,7 +801,7 @@ int span_prefill_fragments(span_plan_t* pl, int32_t layer, const void* q, const 
                                      pl->xch, nch, &pl->prefill_queues, s)
       : pl->split
           ? launch_attn_split(g, pl->tp, nt, pl->kt, q, out, nullptr, nullptr, pl->rope, s)
-               : launch_attn_generic(g, pl->tp, nt, pl->kv, q, out, nullptr, nullptr, pl->rope, s);
+               : launch_attn_generic(g, pl->tp, nt, pl->kv, q, out, nullptr, nullptr, pl->rope, false, s);
   if (e != hipSuccess) return hip_fail(e, "span_prefill_fragments: attention");
   tm.mark(2);
   if (!tm.ev.empty()) pl->ev_prefill.push_back(tm.ev);
@@ -847,7 +847,7 @@ int span_cross_attend(span_plan_t* pl, int32_t layer, const void* q, const void*
   } else if (pl->split) {
     e = launch_attn_split(g, pl->tc, nt, pl->kt, q, out, po, pml, pl->rope, s);
   } else {
-    e = launch_attn_generic(g, pl->tc, nt, pl->kv, q, out, po, pml, pl->rope, s);
+    e = launch_attn_generic(g, pl->tc, nt, pl->kv, q, out, po, pml, pl->rope, true, s);
   }
   if (e != hipSuccess) return hip_fail(e, "span_cross_attend: attention");
   tm.mark(3);
@@ -971,7 +971,7 @@ int span_decode_attend(span_plan_t* pl, int32_t layer, const void* q, const void
   } else if (pl->split) {
     e = launch_attn_split(g, pl->dec.tiles, nt, pl->dec.kt, q, out, po, pml, pl->dec.rope, s);
   } else {
-    e = launch_attn_generic(g, pl->dec.tiles, nt, pl->dec.kv, q, out, po, pml, pl->dec.rope, s);
+    e = launch_attn_generic(g, pl->dec.tiles, nt, pl->dec.kv, q, out, po, pml, pl->dec.rope, true, s);
   }
   if (e != hipSuccess) return hip_fail(e, "span_decode_attend: attention");
   e = launch_combine(g, pl->dec.cb, static_cast<int>(d.combine.size()), po, pml, pl->bm, max_parts(d.combine), out, s);

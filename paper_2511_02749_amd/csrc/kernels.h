@@ -33,9 +33,11 @@ hipError_t launch_move_pages(const PoolGeom& g, const MovePage* moves, int n_mov
 // Generic span attention (any dtype, any heads per kv head) over work tiles of up to
 // kGenericBM rows.
 constexpr int kGenericBM = 64;
+// runs: give each wave its pages in one run of a list (cross and decode lists, whose
+// reposition delta changes along them) and not every few pages (causal prefill lists).
 hipError_t launch_attn_generic(const PoolGeom& g, const WorkTile* tiles, int n_tiles, const KvPage* kv,
                                const void* q, void* out, void* part_o, float* part_ml,
-                               const float2* rope, hipStream_t s);
+                               const float2* rope, bool runs, hipStream_t s);
 
 // bf16 pools at fp32 precision of queries and weights, any number g of query heads per
 // kv head: row tiles of up to split_bm(g) tokens, split_chunks(g) work items per tile and
