@@ -45,8 +45,10 @@
  *   work completes.  A plan's device metadata (and a grown rotary table) are copied
  *   on the stream given to span_plan; an attention call on any other stream first
  *   makes that stream wait (hipStreamWaitEvent) for those copies, and
- *   span_plan_destroy releases the plan's device memory on the plan's stream only
- *   after the work already enqueued on every stream the plan was launched on.
+ *   span_plan_destroy gives the plan's device memory back (to the pool, for later
+ *   plans, or to the device) only after the work already enqueued on every stream
+ *   the plan was launched on.  A pool keeps at most 4 such blocks, 256 MiB in all,
+ *   until it is destroyed.
  * - A pool is not thread-safe; use one thread per pool.
  */
 #ifndef SPANQ_H
@@ -73,7 +75,7 @@ extern "C" {
                              cached (section 2); prefix-only queries, host-only pools */
 
 #define SPAN_KERNEL_AUTO 0    /* bf16 MFMA kernel where the shape allows, else generic */
-#define SPAN_KERNEL_GENERIC 1 /* vector-ALU kernel, any supported shape / dtype */
+#define SPAN_KERNEL_GENERIC 1 /* fp32-precision kernels, any supported shape / dtype */
 #define SPAN_KERNEL_MFMA 2    /* bf16 MFMA kernel: bf16 pools, head_dim 64 or 128, num_q_heads /
                                  num_kv_heads in {1, 2, 4, 8} (SPAN_EINVAL otherwise) */
 
@@ -257,7 +259,7 @@ int span_plan_rows(const span_plan_t* plan, int64_t* rows, int64_t cap, int64_t*
  * same arguments, same kernels; the plan's device data (work lists, scheduling
  * counters, split-KV partials) go to a device array of SPAN_STATIC_SCRATCH_BYTES
  * that the library holds on each GPU until the process ends, instead of the
- * stream-ordered allocations span_plan makes.  No hipMalloc, hipFree or other
+ * stream-ordered allocations span_plan makes (or the block a pool kept of one).  No hipMalloc, hipFree or other
  * device allocation is made by this call or by the attention calls and destroy of
  * its plan.
  * - SPAN_EINVAL if the plan's device data exceed SPAN_STATIC_SCRATCH_BYTES, or if
@@ -306,9 +308,10 @@ int span_cross_attend(span_plan_t* plan, int32_t layer, const void* q, const voi
 int span_plan_commit(span_plan_t* plan);
 
 /* Free the plan.  Without a prior commit its new pages are freed unpublished and its
- * hits unpinned.  Device metadata is released on the plan's stream, ordered after
- * the work enqueued so far on every stream the plan's attention calls used; the
- * call itself does not wait for the device. */
+ * hits unpinned.  The plan's device memory is kept for a later plan of the pool or
+ * released on the plan's stream, ordered after the work enqueued so far on every
+ * stream the plan's attention calls used; the call itself does not wait for the
+ * device. */
 int span_plan_destroy(span_plan_t* plan);
 
 /* ---------------------------------------------------------------- nested generation */

@@ -9,8 +9,8 @@
 namespace spanq {
 
 // span_plan's work.  With region == nullptr the plan's device data (work lists,
-// scheduling counters, split-KV partials) come from the device's stream-ordered
-// allocator and the rotary table grows as needed.  With a region, they are placed
+// scheduling counters, split-KV partials) come from a block the pool kept or the device's
+// stream-ordered allocator, and the rotary table grows as needed.  With a region, they are placed
 // in region[0, region_bytes) (256-byte aligned device memory of the pool's device)
 // and nothing is allocated: SPAN_EINVAL if they do not fit or the table is too
 // short, SPAN_ESTATE while another plan holds the device's region.  `who` names
