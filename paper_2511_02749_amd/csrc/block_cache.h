@@ -1,0 +1,116 @@
+// Device blocks of destroyed plans and finished decode steps, kept for the next ones:
+// freeing and allocating stream-ordered memory cost 27 and 3 us of a 75 us call.  At most
+// kMaxBlocks of them and kMaxBytes in all; released with the pool.
+//
+// Rt is the device runtime (hip_blocks.h; tests give a model of one):
+//   types Stream, Event, Error, with Error{} = success
+//   bool  capturing(Stream)                     the stream is under graph capture
+//   Error alloc(void**, size_t, Stream), void free(void*, Stream)    stream-ordered
+//   Event make_event() (Event{} on failure), void destroy(Event)
+//   Error record(Event, Stream), wait(Stream, Event)
+#pragma once
+#include <cstddef>
+#include <vector>
+
+namespace spanq {
+
+// A block in use.  keep: it may be kept for another user when it is given back.  Memory
+// allocated while a stream was under capture belongs to the graph (it has nothing behind it
+// before the graph's first launch, and its replays reuse it), so it never is.
+struct DevBlock {
+  void* p = nullptr;
+  size_t bytes = 0;
+  bool keep = false;
+};
+
+template <class Rt>
+class BlockCache {
+ public:
+  using Stream = typename Rt::Stream;
+  using Event = typename Rt::Event;
+  using Error = typename Rt::Error;
+  static constexpr size_t kMaxBlocks = 4, kMaxBytes = size_t{256} << 20;
+
+  // Device memory of at least `bytes` for work on stream s: a kept block that fits without
+  // much waste, else a stream-ordered allocation (always that in a stream under capture,
+  // which cannot wait for an event from outside).
+  Error take(size_t bytes, Stream s, DevBlock* out) {
+    const bool captured = Rt::capturing(s);
+    auto best = kept_.end();
+    if (!captured)
+      for (auto it = kept_.begin(); it != kept_.end(); ++it)
+        if (it->bytes >= bytes && it->bytes <= 4 * bytes + (size_t{1} << 20) &&
+            (best == kept_.end() || it->bytes < best->bytes))
+          best = it;
+    if (best != kept_.end()) {
+      const Kept b = *best;
+      const Error e = Rt::wait(s, b.done);
+      if (e != Error{}) return e;
+      spare_.push_back(b.done);
+      kept_.erase(best);
+      *out = DevBlock{b.p, b.bytes, true};
+      return Error{};
+    }
+    const size_t got = (bytes + 0xffff) & ~static_cast<size_t>(0xffff);  // nearby sizes fit the same block later
+    void* p = nullptr;
+    const Error e = Rt::alloc(&p, got, s);
+    *out = e == Error{} ? DevBlock{p, got, !captured} : DevBlock{};
+    return e;
+  }
+
+  // Give a block back after the work enqueued on stream s so far (which every user of the
+  // block has been ordered before): kept for the next taker, else freed on s.
+  void give(const DevBlock& b, Stream s) {
+    if (!b.p) return;
+    Event ev{};
+    if (b.keep && b.bytes <= kMaxBytes && !Rt::capturing(s)) ev = event();
+    if (ev != Event{} && Rt::record(ev, s) != Error{}) {
+      spare_.push_back(ev);
+      ev = Event{};
+    }
+    if (ev == Event{}) {
+      Rt::free(b.p, s);
+      return;
+    }
+    kept_.push_back({b.p, b.bytes, ev});
+    size_t total = 0;
+    for (const Kept& k : kept_) total += k.bytes;
+    while (kept_.size() > kMaxBlocks || total > kMaxBytes) {  // the oldest go
+      const Kept k = kept_.front();
+      kept_.erase(kept_.begin());
+      total -= k.bytes;
+      (void)Rt::wait(s, k.done);
+      Rt::free(k.p, s);
+      spare_.push_back(k.done);
+    }
+  }
+
+  // Free every kept block (nothing on the device uses them any more).
+  void clear(Stream s) {
+    for (const Kept& k : kept_) {
+      Rt::free(k.p, s);
+      Rt::destroy(k.done);
+    }
+    for (Event e : spare_) Rt::destroy(e);
+    kept_.clear();
+    spare_.clear();
+  }
+
+ private:
+  // done: recorded after the last work that used the block; whoever takes it waits for it
+  struct Kept {
+    void* p;
+    size_t bytes;
+    Event done;
+  };
+  Event event() {
+    if (spare_.empty()) return Rt::make_event();
+    const Event e = spare_.back();
+    spare_.pop_back();
+    return e;
+  }
+  std::vector<Kept> kept_;
+  std::vector<Event> spare_;
+};
+
+}  // namespace spanq

@@ -16,6 +16,7 @@
 
 #include "../../include/spanq.h"
 #include "capi_internal.h"
+#include "hip_blocks.h"
 #include "kernels.h"
 #include "planner.h"
 
@@ -56,17 +57,7 @@ struct span_pool {
   // each time, so they add at most its current size.
   std::vector<float2*> rope_retired;
   std::vector<std::vector<float2>> rope_host;
-  // Device blocks of destroyed plans and finished decode steps, for the next ones: freeing
-  // and allocating stream-ordered memory cost 27 and 3 us of a 75 us call.  At most
-  // kMaxBlocks of them and kMaxBlockBytes in all; freed with the pool.  `done` was recorded
-  // after the last work that used the block: whoever takes it waits for that first.
-  struct Block {
-    void* p = nullptr;
-    size_t bytes = 0;
-    hipEvent_t done = nullptr;
-  };
-  static constexpr size_t kMaxBlocks = 4, kMaxBlockBytes = size_t{256} << 20;
-  std::vector<Block> blocks;
+  BlockCache<HipBlocks> blocks;  // of destroyed plans and finished decode steps
 };
 
 namespace {
@@ -131,73 +122,13 @@ hipEvent_t take_order_event(span_pool* p) {
 }
 }  // namespace
 
-namespace {
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();  // (the null stream while another one is captured)
-  return true;
-}
-
-// Device memory of at least `bytes` for work on stream s: a kept block that fits without
-// much waste, else a stream-ordered allocation (always that in a stream under capture,
-// which cannot wait for an event from outside).  *got = the block's size.
-hipError_t take_block(span_pool* p, size_t bytes, hipStream_t s, void** out, size_t* got) {
-  auto best = p->blocks.end();
-  if (!p->blocks.empty() && !capturing(s))
-    for (auto it = p->blocks.begin(); it != p->blocks.end(); ++it)
-      if (it->bytes >= bytes && it->bytes <= 4 * bytes + (size_t{1} << 20) &&
-          (best == p->blocks.end() || it->bytes < best->bytes))
-        best = it;
-  if (best != p->blocks.end()) {
-    const span_pool::Block b = *best;
-    const hipError_t e = hipStreamWaitEvent(s, b.done, 0);
-    if (e != hipSuccess) return e;
-    p->order_cache.push_back(b.done);
-    p->blocks.erase(best);
-    *out = b.p;
-    *got = b.bytes;
-    return hipSuccess;
-  }
-  *got = (bytes + 0xffff) & ~static_cast<size_t>(0xffff);  // nearby sizes fit the same block later
-  return hipMallocAsync(out, *got, s);
-}
-
-// Release a block after the work enqueued on stream s so far (which every user of the
-// block has been ordered before): kept for the next taker, else freed on s.
-void give_block(span_pool* p, void* ptr, size_t bytes, hipStream_t s) {
-  if (!ptr) return;
-  hipEvent_t ev = nullptr;
-  if (bytes <= span_pool::kMaxBlockBytes && !capturing(s)) ev = take_order_event(p);
-  if (ev && hipEventRecord(ev, s) != hipSuccess) {
-    p->order_cache.push_back(ev);
-    ev = nullptr;
-  }
-  if (!ev) {
-    (void)hipFreeAsync(ptr, s);
-    return;
-  }
-  p->blocks.push_back({ptr, bytes, ev});
-  size_t total = 0;
-  for (const span_pool::Block& b : p->blocks) total += b.bytes;
-  while (p->blocks.size() > span_pool::kMaxBlocks || total > span_pool::kMaxBlockBytes) {  // the oldest go
-    const span_pool::Block b = p->blocks.front();
-    p->blocks.erase(p->blocks.begin());
-    total -= b.bytes;
-    (void)hipStreamWaitEvent(s, b.done, 0);
-    (void)hipFreeAsync(b.p, s);
-    p->order_cache.push_back(b.done);
-  }
-}
-}  // namespace
-
 struct span_plan_t {
   span_pool* pool = nullptr;
   Plan plan;
   hipStream_t stream = nullptr;
   std::vector<unsigned char> host_meta;
-  unsigned char* dev_meta = nullptr;  // one block: metadata, then the partials
-  size_t dev_bytes = 0;
+  DevBlock block;                     // metadata, then the partials
+  unsigned char* dev_meta = nullptr;  // the block, or the region of span_plan_static
   float* part = nullptr;  // partial O (fp16 O / l for bf16 pools, fp32 O otherwise) then partial (m, l)
   size_t part_o_elems = 0;
   // device views
@@ -242,8 +173,8 @@ struct span_plan_t {
   // events of decode attention calls made on other streams: the next step and
   // destroy make the decode stream wait for them before the data are freed.
   struct DecodeDev {
-    unsigned char* meta = nullptr;  // one block: metadata, then the partials
-    size_t bytes = 0;
+    DevBlock block;                 // metadata, then the partials
+    unsigned char* meta = nullptr;
     float* part = nullptr;
     size_t part_o_elems = 0;
     const SlotWrite* writes = nullptr;
@@ -447,7 +378,8 @@ int spanq::plan_impl(span_pool* pool, const span_query* qs, int32_t nq, void* st
       e = hipMemcpyAsync(pl->dev_meta, hb.data(), hb.size(), hipMemcpyHostToDevice, pl->stream);
     } else {
       const size_t meta_bytes = (hb.size() + 255) & ~static_cast<size_t>(255);
-      e = take_block(pool, meta_bytes + part_bytes, pl->stream, reinterpret_cast<void**>(&pl->dev_meta), &pl->dev_bytes);
+      e = pool->blocks.take(meta_bytes + part_bytes, pl->stream, &pl->block);
+      pl->dev_meta = static_cast<unsigned char*>(pl->block.p);
       if (e == hipSuccess) e = hipMemcpyAsync(pl->dev_meta, hb.data(), hb.size(), hipMemcpyHostToDevice, pl->stream);
       if (e == hipSuccess && P.n_parts > 0) pl->part = reinterpret_cast<float*>(pl->dev_meta + meta_bytes);
     }
@@ -568,10 +500,7 @@ int span_pool_destroy(span_pool* p) {
   std::vector<span_plan_t*> live(p->plans.begin(), p->plans.end());
   for (span_plan_t* pl : live) span_plan_destroy(pl);
   if (p->cfg.device >= 0) (void)hipDeviceSynchronize();
-  for (const span_pool::Block& b : p->blocks) {
-    (void)hipFreeAsync(b.p, nullptr);
-    (void)hipEventDestroy(b.done);
-  }
+  p->blocks.clear(nullptr);
   for (hipEvent_t e : p->event_cache) (void)hipEventDestroy(e);
   for (hipEvent_t e : p->order_cache) (void)hipEventDestroy(e);
   if (p->rope_tab) (void)hipFree(p->rope_tab);
@@ -904,7 +833,7 @@ int span_plan_decode(span_plan_t* pl, const int32_t* n_new, const int64_t* rows,
   // the previous step's device data are freed once their readers are done
   rc = decode_drain(pl, s, "span_plan_decode");
   if (rc) return rc;
-  give_block(pool, pl->dec.meta, pl->dec.bytes, s);
+  pool->blocks.give(pl->dec.block, s);
   pl->dec = span_plan_t::DecodeDev{};
   rc = ensure_rope_table(pool, P.max_pos + 1, s);
   if (rc) return rc;
@@ -920,7 +849,8 @@ int span_plan_decode(span_plan_t* pl, const int32_t* n_new, const int64_t* rows,
   pl->dec.part_o_elems = static_cast<size_t>(d.n_parts) * pool->cfg.num_q_heads * pl->bm * pool->cfg.head_dim;
   const size_t part_bytes = pl->dec.part_o_elems * part_elem_bytes(pool->cfg.dtype == SPAN_BF16) +
                             static_cast<size_t>(d.n_parts) * pool->cfg.num_q_heads * pl->bm * 2 * sizeof(float);
-  e = take_block(pool, hb.size() + part_bytes, s, reinterpret_cast<void**>(&pl->dec.meta), &pl->dec.bytes);
+  e = pool->blocks.take(hb.size() + part_bytes, s, &pl->dec.block);
+  pl->dec.meta = static_cast<unsigned char*>(pl->dec.block.p);
   if (e == hipSuccess) e = hipMemcpyAsync(pl->dec.meta, hb.data(), hb.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && d.n_parts > 0) pl->dec.part = reinterpret_cast<float*>(pl->dec.meta + hb.size());
   if (e == hipSuccess && !pl->dec_copied) e = hipEventCreateWithFlags(&pl->dec_copied, hipEventDisableTiming);
@@ -1032,7 +962,7 @@ int span_plan_destroy(span_plan_t* pl) {
   release_events(pl->ev_decode, pl->pool->event_cache);
   // decode data: wait for their readers on the plan's stream, then free there
   if (pl->dec.meta || !pl->dec_pending.empty()) (void)decode_drain(pl, pl->stream, "span_plan_destroy");
-  give_block(pl->pool, pl->dec.meta, pl->dec.bytes, pl->stream);
+  pl->pool->blocks.give(pl->dec.block, pl->stream);
   if (pl->dec_ready) pl->pool->order_cache.push_back(pl->dec_ready);
   if (pl->dec_copied) {
     (void)hipEventSynchronize(pl->dec_copied);
@@ -1049,7 +979,7 @@ int span_plan_destroy(span_plan_t* pl) {
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     g_scratch_owner[pl->pool->cfg.device] = nullptr;
   } else {
-    give_block(pl->pool, pl->dev_meta, pl->dev_bytes, pl->stream);
+    pl->pool->blocks.give(pl->block, pl->stream);
   }
   pl->pool->plans.erase(pl);
   delete pl;

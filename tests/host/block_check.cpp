@@ -1,0 +1,128 @@
+// Host-side checks of the device blocks that a pool keeps (csrc/block_cache.h) on a model of
+// a device runtime: streams that are under capture or not, events that hold the point of a
+// stream they were recorded at, and memory that knows who may use it.
+// tests/test_host_blocks.py builds and runs this.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <set>
+
+#include "block_cache.h"
+
+using spanq::BlockCache;
+using spanq::DevBlock;
+
+static int g_fail = 0;
+#define CHECK(cond)                                                        \
+  do {                                                                     \
+    if (!(cond)) {                                                         \
+      std::fprintf(stderr, "FAIL line %d: %s\n", __LINE__, #cond);         \
+      ++g_fail;                                                            \
+    }                                                                      \
+  } while (0)
+
+namespace {
+
+struct StreamModel {
+  bool captured = false;
+  long issued = 0;                        // work items enqueued
+  std::map<const StreamModel*, long> at;  // of each other stream: waited for its items up to here
+};
+struct EventModel {
+  StreamModel* on = nullptr;
+  long point = 0;
+};
+struct Memory {
+  bool graph = false;  // allocated while capturing: the graph's
+  size_t bytes = 0;
+};
+
+struct Model {
+  using Stream = StreamModel*;
+  using Event = EventModel*;
+  using Error = int;
+  static inline std::map<void*, Memory> memory;
+  static inline std::set<EventModel*> events;
+
+  static bool capturing(Stream s) { return s->captured; }
+  static Error alloc(void** p, size_t bytes, Stream s) {
+    *p = std::malloc(1);
+    memory[*p] = Memory{s->captured, bytes};
+    return 0;
+  }
+  static void free(void* p, Stream) {
+    CHECK(memory.count(p) == 1);
+    memory.erase(p);
+    std::free(p);
+  }
+  static Event make_event() { return *events.insert(new EventModel).first; }
+  static void destroy(Event e) {
+    CHECK(events.erase(e) == 1);
+    delete e;
+  }
+  static Error record(Event e, Stream s) {
+    *e = EventModel{s, s->issued};
+    return 0;
+  }
+  static Error wait(Stream s, Event e) {
+    if (e->on && e->on != s) s->at[e->on] = std::max(s->at[e->on], e->point);
+    return 0;
+  }
+};
+using Cache = BlockCache<Model>;
+
+DevBlock take(Cache& c, size_t bytes, StreamModel& s) {
+  DevBlock b;
+  CHECK(c.take(bytes, &s, &b) == 0);
+  CHECK(b.p != nullptr && b.bytes >= bytes && Model::memory.at(b.p).bytes == b.bytes);
+  ++s.issued;
+  return b;
+}
+
+// A block is used again only after the work that used it before, on whatever stream.
+void order() {
+  Cache c;
+  StreamModel a, b;
+  DevBlock x = take(c, 1000, a);
+  a.issued += 5;
+  const long used = a.issued;
+  c.give(x, &a);
+  a.issued += 7;
+  const DevBlock y = take(c, 900, b);
+  CHECK(y.p != x.p || b.at[&a] >= used);
+  c.give(y, &b);
+  c.clear(&a);
+}
+
+// Memory allocated under capture never reaches another user, whenever it is given back;
+// a stream under capture takes no kept block, and its blocks are not kept.
+void capture() {
+  Cache c;
+  StreamModel a, b;
+  DevBlock kept = take(c, 4096, a);
+  c.give(kept, &a);
+  a.captured = true;
+  const DevBlock g = take(c, 4096, a), h = take(c, 4096, a);
+  CHECK(g.p != kept.p && Model::memory.at(g.p).graph);
+  c.give(h, &a);  // while capturing
+  a.captured = false;
+  c.give(g, &a);  // after the capture ended, with or without a launch
+  for (int i = 0; i < 8; ++i) {
+    const DevBlock t = take(c, 4096, i % 2 ? a : b);
+    CHECK(!Model::memory.at(t.p).graph);
+    if (i % 3) c.give(t, i % 2 ? &a : &b);
+    else Model::free(t.p, nullptr);
+  }
+  c.clear(&a);
+}
+
+}  // namespace
+
+int main() {
+  order();
+  capture();
+  CHECK(Model::memory.empty());
+  CHECK(Model::events.empty());
+  if (g_fail == 0) std::printf("all checks passed\n");
+  return g_fail ? 1 : 0;
+}
