@@ -4,6 +4,8 @@
 //
 // Rt is the device runtime (hip_blocks.h; tests give a model of one):
 //   types Stream, Event, Error, with Error{} = success
+//   type  Device: while one lives, its device is the current one (events and memory are made
+//         there, and an event records only on streams of its own device)
 //   bool  capturing(Stream)                     the stream is under graph capture
 //   Error alloc(void**, size_t, Stream), void free(void*, Stream)    stream-ordered
 //   Event make_event() (Event{} on failure), void destroy(Event)
@@ -31,10 +33,13 @@ class BlockCache {
   using Error = typename Rt::Error;
   static constexpr size_t kMaxBlocks = 4, kMaxBytes = size_t{256} << 20;
 
+  explicit BlockCache(int device) : device_(device) {}
+
   // Device memory of at least `bytes` for work on stream s: a kept block that fits without
   // much waste, else a stream-ordered allocation (always that in a stream under capture,
   // which cannot wait for an event from outside).
   Error take(size_t bytes, Stream s, DevBlock* out) {
+    const typename Rt::Device scope(device_);
     const bool captured = Rt::capturing(s);
     auto best = kept_.end();
     if (!captured)
@@ -62,10 +67,11 @@ class BlockCache {
   // block has been ordered before): kept for the next taker, else freed on s.
   void give(const DevBlock& b, Stream s) {
     if (!b.p) return;
+    const typename Rt::Device scope(device_);
     Event ev{};
     if (b.keep && b.bytes <= kMaxBytes && !Rt::capturing(s)) ev = event();
     if (ev != Event{} && Rt::record(ev, s) != Error{}) {
-      spare_.push_back(ev);
+      Rt::destroy(ev);  // (one that would not record is no use to the next block either)
       ev = Event{};
     }
     if (ev == Event{}) {
@@ -87,6 +93,7 @@ class BlockCache {
 
   // Free every kept block (nothing on the device uses them any more).
   void clear(Stream s) {
+    const typename Rt::Device scope(device_);
     for (const Kept& k : kept_) {
       Rt::free(k.p, s);
       Rt::destroy(k.done);
@@ -109,6 +116,7 @@ class BlockCache {
     spare_.pop_back();
     return e;
   }
+  int device_;
   std::vector<Kept> kept_;
   std::vector<Event> spare_;
 };

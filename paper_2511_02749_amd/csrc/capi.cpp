@@ -39,7 +39,8 @@ size_t elem_size(int32_t dtype) { return dtype == SPAN_BF16 ? 2 : 4; }
 }  // namespace
 
 struct span_pool {
-  span_pool_config cfg{};
+  explicit span_pool(const span_pool_config& c) : cfg(c), blocks(c.device) {}
+  span_pool_config cfg;
   PoolIndex* index = nullptr;
   void* dev = nullptr;
   bool owns_dev = false;
@@ -439,9 +440,8 @@ int span_pool_create(const span_pool_config* c, span_pool** out) {
       return fail(SPAN_EINVAL, "span_pool_create: the MFMA kernel does not support this dtype/shape");
   }
   if (c->kernel < SPAN_KERNEL_AUTO || c->kernel > SPAN_KERNEL_MFMA) return fail(SPAN_EINVAL, "span_pool_create: kernel");
-  span_pool* p = new (std::nothrow) span_pool();
+  span_pool* p = new (std::nothrow) span_pool(*c);
   if (!p) return fail(SPAN_ENOMEM, "span_pool_create: host allocation");
-  p->cfg = *c;
   if (c->device >= 0) {
     size_t need = 0;
     span_pool_bytes(c, &need);
@@ -499,6 +499,7 @@ int span_pool_destroy(span_pool* p) {
   if (!p) return fail(SPAN_EINVAL, "span_pool_destroy: null pool");
   std::vector<span_plan_t*> live(p->plans.begin(), p->plans.end());
   for (span_plan_t* pl : live) span_plan_destroy(pl);
+  const DeviceScope device(p->cfg.device);
   if (p->cfg.device >= 0) (void)hipDeviceSynchronize();
   p->blocks.clear(nullptr);
   for (hipEvent_t e : p->event_cache) (void)hipEventDestroy(e);
@@ -956,6 +957,7 @@ int span_plan_commit(span_plan_t* pl) {
 
 int span_plan_destroy(span_plan_t* pl) {
   if (!pl) return fail(SPAN_EINVAL, "span_plan_destroy: null plan");
+  const DeviceScope device(pl->pool->cfg.device);  // the caller may be on another one
   if (!pl->committed) pl->pool->index->release(&pl->plan);
   release_events(pl->ev_prefill, pl->pool->event_cache);
   release_events(pl->ev_cross, pl->pool->event_cache);

@@ -6,10 +6,29 @@
 
 namespace spanq {
 
+// Makes `device` the current one (none for a host-only pool's -1) until it goes out of scope.
+class DeviceScope {
+ public:
+  explicit DeviceScope(int device) {
+    if (device < 0 || hipGetDevice(&before_) != hipSuccess || before_ == device) return;
+    changed_ = hipSetDevice(device) == hipSuccess;
+  }
+  ~DeviceScope() {
+    if (changed_) (void)hipSetDevice(before_);
+  }
+  DeviceScope(const DeviceScope&) = delete;
+  DeviceScope& operator=(const DeviceScope&) = delete;
+
+ private:
+  int before_ = -1;
+  bool changed_ = false;
+};
+
 struct HipBlocks {
   using Stream = hipStream_t;
   using Event = hipEvent_t;
   using Error = hipError_t;
+  using Device = DeviceScope;
   static bool capturing(Stream s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
@@ -23,7 +42,11 @@ struct HipBlocks {
     return hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess ? e : nullptr;
   }
   static void destroy(Event e) { (void)hipEventDestroy(e); }
-  static Error record(Event e, Stream s) { return hipEventRecord(e, s); }
+  static Error record(Event e, Stream s) {
+    const hipError_t r = hipEventRecord(e, s);
+    if (r != hipSuccess) (void)hipGetLastError();  // handled by the caller: not for the next launch's check to find
+    return r;
+  }
   static Error wait(Stream s, Event e) { return hipStreamWaitEvent(s, e, 0); }
 };
 

@@ -1,6 +1,6 @@
 // Host-side checks of the device blocks that a pool keeps (csrc/block_cache.h) on a model of
 // a device runtime: streams that are under capture or not, events that hold the point of a
-// stream they were recorded at, and memory that knows who may use it.
+// stream they were recorded at, several devices, and memory that knows who may use it.
 // tests/test_host_blocks.py builds and runs this.
 #include <cstdio>
 #include <cstdlib>
@@ -23,12 +23,16 @@ static int g_fail = 0;
 
 namespace {
 
+int g_device = 0;  // the current one
+
 struct StreamModel {
+  int device = 0;
   bool captured = false;
   long issued = 0;                        // work items enqueued
   std::map<const StreamModel*, long> at;  // of each other stream: waited for its items up to here
 };
 struct EventModel {
+  int device = 0;
   StreamModel* on = nullptr;
   long point = 0;
 };
@@ -43,9 +47,15 @@ struct Model {
   using Error = int;
   static inline std::map<void*, Memory> memory;
   static inline std::set<EventModel*> events;
+  struct Device {
+    int before = g_device;
+    explicit Device(int d) { g_device = d; }
+    ~Device() { g_device = before; }
+  };
 
   static bool capturing(Stream s) { return s->captured; }
   static Error alloc(void** p, size_t bytes, Stream s) {
+    CHECK(g_device == s->device);
     *p = std::malloc(1);
     memory[*p] = Memory{s->captured, bytes};
     return 0;
@@ -55,13 +65,21 @@ struct Model {
     memory.erase(p);
     std::free(p);
   }
-  static Event make_event() { return *events.insert(new EventModel).first; }
+  static inline int refuse_records = 0;  // how many records fail from now on
+  static Event make_event() { return *events.insert(new EventModel{g_device, nullptr, 0}).first; }
   static void destroy(Event e) {
     CHECK(events.erase(e) == 1);
     delete e;
   }
   static Error record(Event e, Stream s) {
-    *e = EventModel{s, s->issued};
+    CHECK(events.count(e) == 1);
+    if (e->device != s->device) return 1;
+    if (refuse_records > 0) {
+      --refuse_records;
+      return 1;
+    }
+    e->on = s;
+    e->point = s->issued;
     return 0;
   }
   static Error wait(Stream s, Event e) {
@@ -81,7 +99,7 @@ DevBlock take(Cache& c, size_t bytes, StreamModel& s) {
 
 // A block is used again only after the work that used it before, on whatever stream.
 void order() {
-  Cache c;
+  Cache c(0);
   StreamModel a, b;
   DevBlock x = take(c, 1000, a);
   a.issued += 5;
@@ -97,7 +115,7 @@ void order() {
 // Memory allocated under capture never reaches another user, whenever it is given back;
 // a stream under capture takes no kept block, and its blocks are not kept.
 void capture() {
-  Cache c;
+  Cache c(0);
   StreamModel a, b;
   DevBlock kept = take(c, 4096, a);
   c.give(kept, &a);
@@ -116,11 +134,50 @@ void capture() {
   c.clear(&a);
 }
 
+// Pools on two devices in one thread: a block is given back while the other device is the
+// current one, which it still is afterwards, and is kept all the same.
+void devices() {
+  Cache c(1);
+  StreamModel s;
+  s.device = 1;
+  g_device = 0;
+  DevBlock x = take(c, 70000, s);
+  for (int i = 0; i < 3; ++i) {
+    c.give(x, &s);
+    CHECK(g_device == 0);
+    const DevBlock y = take(c, 70000, s);
+    CHECK(y.p == x.p);
+    x = y;
+  }
+  c.give(x, &s);
+  c.clear(&s);
+  CHECK(g_device == 0);
+}
+
+// An event that would not record costs one block, not the keeping of blocks from then on.
+void refused_record() {
+  Cache c(0);
+  StreamModel s;
+  DevBlock x = take(c, 70000, s);
+  Model::refuse_records = 1;
+  c.give(x, &s);
+  CHECK(Model::memory.count(x.p) == 0);  // freed
+  CHECK(Model::events.empty());          // and its event not left for the next block
+  x = take(c, 70000, s);
+  c.give(x, &s);
+  const DevBlock y = take(c, 70000, s);
+  CHECK(y.p == x.p);
+  c.give(y, &s);
+  c.clear(&s);
+}
+
 }  // namespace
 
 int main() {
   order();
   capture();
+  devices();
+  refused_record();
   CHECK(Model::memory.empty());
   CHECK(Model::events.empty());
   if (g_fail == 0) std::printf("all checks passed\n");
