@@ -10,6 +10,7 @@
 //   Error alloc(void**, size_t, Stream), void free(void*, Stream)    stream-ordered
 //   Event make_event() (Event{} on failure), void destroy(Event)
 //   Error record(Event, Stream), wait(Stream, Event)
+//   bool  done(Event)                           the work it was recorded after has ended
 #pragma once
 #include <cstddef>
 #include <vector>
@@ -36,8 +37,9 @@ class BlockCache {
   explicit BlockCache(int device) : device_(device) {}
 
   // Device memory of at least `bytes` for work on stream s: a kept block that fits without
-  // much waste, else a stream-ordered allocation (always that in a stream under capture,
-  // which cannot wait for an event from outside).
+  // much waste and that s need not wait for (given back on s, or after work that has ended),
+  // else a stream-ordered allocation (always that in a stream under capture, which cannot
+  // wait for an event from outside).
   Error take(size_t bytes, Stream s, DevBlock* out) {
     const typename Rt::Device scope(device_);
     const bool captured = Rt::capturing(s);
@@ -45,7 +47,7 @@ class BlockCache {
     if (!captured)
       for (auto it = kept_.begin(); it != kept_.end(); ++it)
         if (it->bytes >= bytes && it->bytes <= 4 * bytes + (size_t{1} << 20) &&
-            (best == kept_.end() || it->bytes < best->bytes))
+            (best == kept_.end() || it->bytes < best->bytes) && free_for(*it, s))
           best = it;
     if (best != kept_.end()) {
       const Kept b = *best;
@@ -78,17 +80,27 @@ class BlockCache {
       Rt::free(b.p, s);
       return;
     }
-    kept_.push_back({b.p, b.bytes, ev});
-    size_t total = 0;
+    // Room for it: the oldest that s need not wait for go.  If that is not enough, this one
+    // goes instead: no stream waits for another one's work on account of the list.
+    size_t total = b.bytes;
     for (const Kept& k : kept_) total += k.bytes;
-    while (kept_.size() > kMaxBlocks || total > kMaxBytes) {  // the oldest go
-      const Kept k = kept_.front();
-      kept_.erase(kept_.begin());
-      total -= k.bytes;
-      (void)Rt::wait(s, k.done);
-      Rt::free(k.p, s);
-      spare_.push_back(k.done);
+    for (auto it = kept_.begin(); (kept_.size() >= kMaxBlocks || total > kMaxBytes) && it != kept_.end();) {
+      if (!free_for(*it, s)) {
+        ++it;
+        continue;
+      }
+      total -= it->bytes;
+      (void)Rt::wait(s, it->done);
+      Rt::free(it->p, s);
+      spare_.push_back(it->done);
+      it = kept_.erase(it);
     }
+    if (kept_.size() >= kMaxBlocks || total > kMaxBytes) {
+      Rt::free(b.p, s);
+      spare_.push_back(ev);
+      return;
+    }
+    kept_.push_back({b.p, b.bytes, ev, s});
   }
 
   // Free every kept block (nothing on the device uses them any more).
@@ -104,12 +116,16 @@ class BlockCache {
   }
 
  private:
-  // done: recorded after the last work that used the block; whoever takes it waits for it
+  // done: recorded, on stream `by`, after the last work that used the block; whoever takes it
+  // waits for it.  (`by` is only compared: the stream may be gone, and another one in its place
+  // costs a wait at most.)
   struct Kept {
     void* p;
     size_t bytes;
     Event done;
+    Stream by;
   };
+  static bool free_for(const Kept& k, Stream s) { return k.by == s || Rt::done(k.done); }
   Event event() {
     if (spare_.empty()) return Rt::make_event();
     const Event e = spare_.back();

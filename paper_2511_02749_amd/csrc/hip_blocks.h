@@ -47,6 +47,15 @@ struct HipBlocks {
     if (r != hipSuccess) (void)hipGetLastError();  // handled by the caller: not for the next launch's check to find
     return r;
   }
+  static bool done(Event e) {
+    // relaxed: the thread may be capturing some other stream, which a query must not disturb
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t r = hipEventQuery(e);
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (r != hipSuccess) (void)hipGetLastError();  // (hipErrorNotReady)
+    return r == hipSuccess;
+  }
   static Error wait(Stream s, Event e) { return hipStreamWaitEvent(s, e, 0); }
 };
 

@@ -28,7 +28,7 @@ int g_device = 0;  // the current one
 struct StreamModel {
   int device = 0;
   bool captured = false;
-  long issued = 0;                        // work items enqueued
+  long issued = 0, ended = 0;             // work items enqueued, and done
   std::map<const StreamModel*, long> at;  // of each other stream: waited for its items up to here
 };
 struct EventModel {
@@ -82,6 +82,7 @@ struct Model {
     e->point = s->issued;
     return 0;
   }
+  static bool done(Event e) { return !e->on || e->on->ended >= e->point; }
   static Error wait(Stream s, Event e) {
     if (e->on && e->on != s) s->at[e->on] = std::max(s->at[e->on], e->point);
     return 0;
@@ -106,10 +107,66 @@ void order() {
   const long used = a.issued;
   c.give(x, &a);
   a.issued += 7;
+  a.ended = used;
   const DevBlock y = take(c, 900, b);
-  CHECK(y.p != x.p || b.at[&a] >= used);
+  CHECK(y.p == x.p && b.at[&a] >= used);
   c.give(y, &b);
   c.clear(&a);
+}
+
+// A stream never waits for the work of another one on account of a kept block: not when it
+// takes one, and not when it gives one back to a full list.
+void independent_streams() {
+  Cache c(0);
+  StreamModel a, b;
+  DevBlock x[Cache::kMaxBlocks];
+  for (DevBlock& t : x) t = take(c, 70000, a);
+  a.issued += 100;  // long work, not done yet
+  for (const DevBlock& t : x) c.give(t, &a);
+  const DevBlock y = take(c, 70000, b);
+  for (const DevBlock& t : x) CHECK(y.p != t.p);
+  c.give(y, &b);  // the list is full of a's blocks
+  CHECK(b.at.count(&a) == 0);
+  const DevBlock z = take(c, 70000, a);  // a may have its own back at any time
+  bool own = false;
+  for (const DevBlock& t : x) own = own || z.p == t.p;
+  CHECK(own);
+  c.give(z, &a);
+  a.ended = a.issued;  // its work is done: b may have them, and take their places
+  const DevBlock w = take(c, 70000, b), v = take(c, 1000000, b);
+  own = false;
+  for (const DevBlock& t : x) own = own || w.p == t.p;
+  CHECK(own);
+  c.give(w, &b);
+  c.give(v, &b);
+  const DevBlock u = take(c, 1000000, b);
+  CHECK(u.p == v.p);
+  c.give(u, &b);
+  CHECK(Model::memory.size() == Cache::kMaxBlocks);
+  c.clear(&a);
+}
+
+// At most kMaxBlocks blocks and kMaxBytes in all are kept, and no larger one.
+void bounds() {
+  Cache c(0);
+  StreamModel s;
+  const size_t half = Cache::kMaxBytes / 2;
+  DevBlock x[8];
+  for (int i = 0; i < 8; ++i) x[i] = take(c, i < 3 ? half : 70000, s);
+  for (const DevBlock& t : x) {
+    c.give(t, &s);
+    size_t kept = 0, n = 0;
+    for (const DevBlock& k : x)
+      if (&k <= &t && Model::memory.count(k.p)) {
+        kept += k.bytes;
+        ++n;
+      }
+    CHECK(kept <= Cache::kMaxBytes && n <= Cache::kMaxBlocks && n >= 1);
+  }
+  const DevBlock big = take(c, Cache::kMaxBytes + 1, s);
+  c.give(big, &s);
+  CHECK(Model::memory.count(big.p) == 0);
+  c.clear(&s);
 }
 
 // Memory allocated under capture never reaches another user, whenever it is given back;
@@ -175,6 +232,8 @@ void refused_record() {
 
 int main() {
   order();
+  independent_streams();
+  bounds();
   capture();
   devices();
   refused_record();
