@@ -48,7 +48,7 @@
  *   span_plan_destroy gives the plan's device memory back (to the pool, for later
  *   plans, or to the device) only after the work already enqueued on every stream
  *   the plan was launched on.  A pool keeps at most 4 such blocks, 256 MiB in all,
- *   until it is destroyed.
+ *   until it is destroyed, or until an allocation of a pool on the device fails.
  * - A pool is not thread-safe; use one thread per pool.
  */
 #ifndef SPANQ_H

@@ -13,6 +13,7 @@
 //   bool  done(Event)                           the work it was recorded after has ended
 #pragma once
 #include <cstddef>
+#include <mutex>
 #include <vector>
 
 namespace spanq {
@@ -34,33 +35,34 @@ class BlockCache {
   using Error = typename Rt::Error;
   static constexpr size_t kMaxBlocks = 4, kMaxBytes = size_t{256} << 20;
 
-  explicit BlockCache(int device) : device_(device) {}
+  explicit BlockCache(int device) : device_(device) {
+    std::lock_guard<std::mutex> lock(all_mu_);
+    next_ = first_;
+    first_ = this;
+  }
+  ~BlockCache() {
+    std::lock_guard<std::mutex> lock(all_mu_);
+    BlockCache** at = &first_;
+    while (*at != this) at = &(*at)->next_;
+    *at = next_;
+  }
+  BlockCache(const BlockCache&) = delete;
+  BlockCache& operator=(const BlockCache&) = delete;
 
   // Device memory of at least `bytes` for work on stream s: a kept block that fits without
   // much waste and that s need not wait for (given back on s, or after work that has ended),
   // else a stream-ordered allocation (always that in a stream under capture, which cannot
-  // wait for an event from outside).
+  // wait for an event from outside).  If that fails, what the caches of the device keep is
+  // freed, this one's and other pools', and it is tried once more: keeping blocks makes no call
+  // fail that passes without.
   Error take(size_t bytes, Stream s, DevBlock* out) {
     const typename Rt::Device scope(device_);
     const bool captured = Rt::capturing(s);
-    auto best = kept_.end();
-    if (!captured)
-      for (auto it = kept_.begin(); it != kept_.end(); ++it)
-        if (it->bytes >= bytes && it->bytes <= 4 * bytes + (size_t{1} << 20) &&
-            (best == kept_.end() || it->bytes < best->bytes) && free_for(*it, s))
-          best = it;
-    if (best != kept_.end()) {
-      const Kept b = *best;
-      const Error e = Rt::wait(s, b.done);
-      if (e != Error{}) return e;
-      spare_.push_back(b.done);
-      kept_.erase(best);
-      *out = DevBlock{b.p, b.bytes, true};
-      return Error{};
-    }
+    if (!captured && take_kept(bytes, s, out)) return Error{};
     const size_t got = (bytes + 0xffff) & ~static_cast<size_t>(0xffff);  // nearby sizes fit the same block later
     void* p = nullptr;
-    const Error e = Rt::alloc(&p, got, s);
+    Error e = Rt::alloc(&p, got, s);
+    if (e != Error{} && !captured && free_all_kept(s)) e = Rt::alloc(&p, got, s);
     *out = e == Error{} ? DevBlock{p, got, !captured} : DevBlock{};
     return e;
   }
@@ -70,6 +72,7 @@ class BlockCache {
   void give(const DevBlock& b, Stream s) {
     if (!b.p) return;
     const typename Rt::Device scope(device_);
+    std::lock_guard<std::mutex> lock(mu_);
     Event ev{};
     if (b.keep && b.bytes <= kMaxBytes && !Rt::capturing(s)) ev = event();
     if (ev != Event{} && Rt::record(ev, s) != Error{}) {
@@ -106,6 +109,7 @@ class BlockCache {
   // Free every kept block (nothing on the device uses them any more).
   void clear(Stream s) {
     const typename Rt::Device scope(device_);
+    std::lock_guard<std::mutex> lock(mu_);
     for (const Kept& k : kept_) {
       Rt::free(k.p, s);
       Rt::destroy(k.done);
@@ -126,13 +130,51 @@ class BlockCache {
     Stream by;
   };
   static bool free_for(const Kept& k, Stream s) { return k.by == s || Rt::done(k.done); }
+  bool take_kept(size_t bytes, Stream s, DevBlock* out) {
+    std::lock_guard<std::mutex> lock(mu_);
+    auto best = kept_.end();
+    for (auto it = kept_.begin(); it != kept_.end(); ++it)
+      if (it->bytes >= bytes && it->bytes <= 4 * bytes + (size_t{1} << 20) &&
+          (best == kept_.end() || it->bytes < best->bytes) && free_for(*it, s))
+        best = it;
+    if (best == kept_.end() || Rt::wait(s, best->done) != Error{}) return false;
+    *out = DevBlock{best->p, best->bytes, true};
+    spare_.push_back(best->done);
+    kept_.erase(best);
+    return true;
+  }
+
+  // Free, on stream s, every block that a cache of this device keeps; whether there was one.
+  bool free_all_kept(Stream s) {
+    std::lock_guard<std::mutex> lock(all_mu_);
+    bool any = false;
+    for (BlockCache* c = first_; c; c = c->next_) {
+      if (c->device_ != device_) continue;
+      std::lock_guard<std::mutex> own(c->mu_);
+      for (const Kept& k : c->kept_) {
+        (void)Rt::wait(s, k.done);
+        Rt::free(k.p, s);
+        c->spare_.push_back(k.done);
+        any = true;
+      }
+      c->kept_.clear();
+    }
+    return any;
+  }
+
   Event event() {
     if (spare_.empty()) return Rt::make_event();
     const Event e = spare_.back();
     spare_.pop_back();
     return e;
   }
+  // every cache of the process
+  static inline std::mutex all_mu_;
+  static inline BlockCache* first_ = nullptr;
+  BlockCache* next_ = nullptr;
+
   int device_;
+  std::mutex mu_;  // a pool is one thread's, but another pool's thread may free what this one keeps
   std::vector<Kept> kept_;
   std::vector<Event> spare_;
 };

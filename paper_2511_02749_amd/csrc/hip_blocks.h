@@ -35,7 +35,11 @@ struct HipBlocks {
     (void)hipGetLastError();  // (the null stream while another one is captured)
     return true;
   }
-  static Error alloc(void** p, size_t bytes, Stream s) { return hipMallocAsync(p, bytes, s); }
+  static Error alloc(void** p, size_t bytes, Stream s) {
+    const hipError_t r = hipMallocAsync(p, bytes, s);
+    if (r != hipSuccess) (void)hipGetLastError();  // returned, and perhaps mended by a second try
+    return r;
+  }
   static void free(void* p, Stream s) { (void)hipFreeAsync(p, s); }
   static Event make_event() {
     hipEvent_t e = nullptr;

@@ -1,6 +1,6 @@
 // Host-side checks of the device blocks that a pool keeps (csrc/block_cache.h) on a model of
 // a device runtime: streams that are under capture or not, events that hold the point of a
-// stream they were recorded at, several devices, and memory that knows who may use it.
+// stream they were recorded at, several devices, and a limited memory that knows who may use it.
 // tests/test_host_blocks.py builds and runs this.
 #include <cstdio>
 #include <cstdlib>
@@ -38,6 +38,7 @@ struct EventModel {
 };
 struct Memory {
   bool graph = false;  // allocated while capturing: the graph's
+  int device = 0;
   size_t bytes = 0;
 };
 
@@ -47,6 +48,7 @@ struct Model {
   using Error = int;
   static inline std::map<void*, Memory> memory;
   static inline std::set<EventModel*> events;
+  static inline size_t limit = size_t(-1);  // bytes a device has
   struct Device {
     int before = g_device;
     explicit Device(int d) { g_device = d; }
@@ -56,8 +58,11 @@ struct Model {
   static bool capturing(Stream s) { return s->captured; }
   static Error alloc(void** p, size_t bytes, Stream s) {
     CHECK(g_device == s->device);
+    size_t used = 0;
+    for (const auto& m : memory) used += m.second.device == s->device ? m.second.bytes : 0;
+    if (used + bytes > limit) return 2;
     *p = std::malloc(1);
-    memory[*p] = Memory{s->captured, bytes};
+    memory[*p] = Memory{s->captured, s->device, bytes};
     return 0;
   }
   static void free(void* p, Stream) {
@@ -191,6 +196,34 @@ void capture() {
   c.clear(&a);
 }
 
+// Near the memory limit an allocation passes that would pass if nothing were kept, whichever
+// pool of the device keeps it; one that is too large fails, and leaves nothing in use.
+void limit() {
+  Cache c(0), other(0), far(1);
+  StreamModel a, b, f;
+  f.device = 1;
+  const size_t mb = size_t{1} << 20;
+  Model::limit = 100 * mb;
+  c.give(take(c, 40 * mb, a), &a);
+  other.give(take(other, 40 * mb, b), &b);
+  const DevBlock there = take(far, 40 * mb, f);
+  far.give(there, &f);
+  ++b.issued;
+  DevBlock x;
+  CHECK(c.take(90 * mb, &a, &x) == 0 && x.p != nullptr);
+  CHECK(a.at[&b] >= 1);                       // what the other pool's stream had done with its block
+  CHECK(Model::memory.count(there.p) == 1);   // another device's memory is no help
+  DevBlock y;
+  CHECK(c.take(90 * mb, &a, &y) != 0 && y.p == nullptr);
+  c.give(x, &a);
+  CHECK(take(c, 90 * mb, a).p == x.p);
+  c.give(x, &a);
+  c.clear(&a);
+  other.clear(&b);
+  far.clear(&f);
+  Model::limit = size_t(-1);
+}
+
 // Pools on two devices in one thread: a block is given back while the other device is the
 // current one, which it still is afterwards, and is kept all the same.
 void devices() {
@@ -235,6 +268,7 @@ int main() {
   independent_streams();
   bounds();
   capture();
+  limit();
   devices();
   refused_record();
   CHECK(Model::memory.empty());
