@@ -510,10 +510,11 @@ int gemv_slices(int N, int K, int* rows) {
   return (K + *rows - 1) / *rows;
 }
 
-// Pass 1 of the GEMV; returns the number of K slices (0 on a launch error).
-int gemv_pass1(const void* x, const void* w, int M, int N, int K, float* part, hipStream_t s) {
+// Pass 1 of the GEMV; *chunks = the number of K slices.  (The launch error is returned from
+// here: asking for it clears it.)
+hipError_t gemv_pass1(const void* x, const void* w, int M, int N, int K, float* part, int* chunks, hipStream_t s) {
   int rows = 0;
-  const int slices = gemv_slices(N, K, &rows);
+  const int slices = *chunks = gemv_slices(N, K, &rows);
   const u16* xx = static_cast<const u16*>(x);
   const uint4* ww = static_cast<const uint4*>(w);
   auto go = [&](auto mp) {
@@ -529,7 +530,7 @@ int gemv_pass1(const void* x, const void* w, int M, int N, int K, float* part, h
   else if (M == 2) go(std::integral_constant<int, 2>{});
   else if (M <= 4) go(std::integral_constant<int, 4>{});
   else go(std::integral_constant<int, 8>{});
-  return hipGetLastError() == hipSuccess ? slices : 0;
+  return hipGetLastError();
 }
 
 bool gemv_args_ok(int M, int N, int K, size_t part_bytes) {
@@ -549,14 +550,16 @@ int lm_head_chunks(int hidden, int vocab) {
 
 hipError_t launch_lm_head(const void* nf, const void* w, float* part, int nq, int hidden, int vocab, hipStream_t s) {
   if (nq < 1 || nq > 8 || vocab % 8 != 0) return hipErrorInvalidValue;
-  return gemv_pass1(nf, w, nq, vocab, hidden, part, s) ? hipSuccess : hipGetLastError();
+  int chunks = 0;
+  return gemv_pass1(nf, w, nq, vocab, hidden, part, &chunks, s);
 }
 
 hipError_t launch_gemv(const void* x, const void* w, void* y, int M, int N, int K, bool residual, float* part,
                        size_t part_bytes, hipStream_t s) {
   if (!gemv_args_ok(M, N, K, part_bytes)) return hipErrorInvalidValue;
-  const int chunks = gemv_pass1(x, w, M, N, K, part, s);
-  if (!chunks) return hipGetLastError();
+  int chunks = 0;
+  const hipError_t e = gemv_pass1(x, w, M, N, K, part, &chunks, s);
+  if (e != hipSuccess) return e;
   const int64_t items = static_cast<int64_t>(M) * N;
   gemv_reduce_kernel<<<static_cast<int>((items + 255) / 256), 256, 0, s>>>(part, chunks, M, N, static_cast<u16*>(y),
                                                                            residual);
@@ -567,8 +570,9 @@ hipError_t launch_gemv_qkv(const void* x, const void* w, int M, int K, const int
                            int kv_elems, void* q, void* k, void* v, float* part, size_t part_bytes, hipStream_t s) {
   const int N = q_elems + 2 * kv_elems;
   if (!gemv_args_ok(M, N, K, part_bytes)) return hipErrorInvalidValue;
-  const int chunks = gemv_pass1(x, w, M, N, K, part, s);
-  if (!chunks) return hipGetLastError();
+  int chunks = 0;
+  const hipError_t e = gemv_pass1(x, w, M, N, K, part, &chunks, s);
+  if (e != hipSuccess) return e;
   const int64_t items = static_cast<int64_t>(M) * N;
   gemv_reduce_qkv_kernel<<<static_cast<int>((items + 255) / 256), 256, 0, s>>>(
       part, chunks, M, N, rows, q_elems, kv_elems, static_cast<u16*>(q), static_cast<u16*>(k), static_cast<u16*>(v));
@@ -578,8 +582,9 @@ hipError_t launch_gemv_qkv(const void* x, const void* w, int M, int K, const int
 hipError_t launch_gemv_swiglu(const void* x, const void* w, void* act, int M, int ffn, int K, float* part,
                               size_t part_bytes, hipStream_t s) {
   if (!gemv_args_ok(M, 2 * ffn, K, part_bytes)) return hipErrorInvalidValue;
-  const int chunks = gemv_pass1(x, w, M, 2 * ffn, K, part, s);
-  if (!chunks) return hipGetLastError();
+  int chunks = 0;
+  const hipError_t e = gemv_pass1(x, w, M, 2 * ffn, K, part, &chunks, s);
+  if (e != hipSuccess) return e;
   const int64_t items = static_cast<int64_t>(M) * ffn;
   gemv_reduce_swiglu_kernel<<<static_cast<int>((items + 255) / 256), 256, 0, s>>>(part, chunks, M, ffn,
                                                                                   static_cast<u16*>(act));
@@ -589,8 +594,9 @@ hipError_t launch_gemv_swiglu(const void* x, const void* w, void* act, int M, in
 hipError_t launch_gemv_residual_norm(const void* x, const void* w, void* y, int M, int N, int K, const void* gain,
                                      void* nout, float eps, float* part, size_t part_bytes, hipStream_t s) {
   if (!gemv_args_ok(M, N, K, part_bytes) || N > kNormThreads * kNormVec * 8) return hipErrorInvalidValue;
-  const int chunks = gemv_pass1(x, w, M, N, K, part, s);
-  if (!chunks) return hipGetLastError();
+  int chunks = 0;
+  const hipError_t e = gemv_pass1(x, w, M, N, K, part, &chunks, s);
+  if (e != hipSuccess) return e;
   gemv_reduce_norm_kernel<<<static_cast<unsigned>(M), kNormThreads, 0, s>>>(
       part, chunks, M, N, static_cast<u16*>(y), static_cast<const uint4*>(gain), static_cast<uint4*>(nout), eps);
   return hipGetLastError();

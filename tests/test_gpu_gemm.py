@@ -13,6 +13,8 @@ the skinny MFMA kernel (K split into slices that add up in a fixed order when N 
 tiles are few); the test also runs shapes and row counts on either side of it (the
 GEMV kernels up to 8 rows, hipBLASLt for the rest).
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -99,3 +101,21 @@ def test_gemv_tiles_and_slices(M, N, K):
     them), of its row groups (K not a multiple of 16 or of a slice) and of its slices of
     K (one short slice to many)."""
     assert _run(M, N, K, residual=True, seed=M + N + K) == 1
+
+
+def test_a_launch_error_is_reported():
+    """An error that stands when the GEMV's first pass is launched (here one that an earlier,
+    refused call of the runtime left: no kernel is involved) is returned; the call does not
+    report success with its second pass left out.  The next call runs."""
+    hip = ctypes.CDLL(spanq._lib.library_path())  # the runtime that the library is linked to
+    x = torch.ones((1, 64), dtype=torch.bfloat16, device="cuda")
+    w = torch.ones((64, 64), dtype=torch.bfloat16, device="cuda")
+    y = torch.zeros((1, 64), dtype=torch.bfloat16, device="cuda")
+    hip.hipGetLastError()
+    assert hip.hipSetDevice(1 << 20) != 0 and hip.hipPeekAtLastError() != 0
+    with pytest.raises(spanq.SpanError):
+        spanq._lib.probe_gemm(x, w, y)
+    hip.hipGetLastError()
+    assert spanq._lib.probe_gemm(x, w, y)[0] == 1
+    torch.cuda.synchronize()
+    assert (y == 64).all()
