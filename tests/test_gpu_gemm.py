@@ -107,7 +107,7 @@ def test_a_launch_error_is_reported():
     """An error that stands when the GEMV's first pass is launched (here one that an earlier,
     refused call of the runtime left: no kernel is involved) is returned; the call does not
     report success with its second pass left out.  The next call runs."""
-    hip = ctypes.CDLL(spanq._lib.library_path())  # the runtime that the library is linked to
+    hip = ctypes.CDLL(spanq._lib.library_path())  # finds the runtime that it is linked to
     x = torch.ones((1, 64), dtype=torch.bfloat16, device="cuda")
     w = torch.ones((64, 64), dtype=torch.bfloat16, device="cuda")
     y = torch.zeros((1, 64), dtype=torch.bfloat16, device="cuda")
