@@ -1,12 +1,12 @@
 // Host-side page cache index and span planner (no HIP dependency).
 #pragma once
 #include <cstdint>
-#include <set>
 #include <string>
 #include <tuple>
 #include <unordered_map>
 #include <vector>
 
+#include "id_set.h"
 #include "work.h"
 
 namespace spanq {
@@ -102,42 +102,6 @@ inline Tiling tiling_split(int bm, int items_per_tile) {
   t.pad4 = true;
   return t;
 }
-
-// A set of ids in [0, n) as a bitmap, with a bit per word over it: lowest member,
-// insertion and removal touch a word of each.
-class IdSet {
- public:
-  void resize(int64_t n) {
-    words_.assign(static_cast<size_t>((n + 63) / 64), 0);
-    top_.assign((words_.size() + 63) / 64, 0);
-    size_ = 0;
-  }
-  bool empty() const { return size_ == 0; }
-  int64_t size() const { return size_; }
-  bool contains(int64_t i) const { return (words_[i >> 6] >> (i & 63)) & 1; }
-  void insert(int32_t i) {  // not a member yet
-    words_[i >> 6] |= uint64_t{1} << (i & 63);
-    top_[i >> 12] |= uint64_t{1} << ((i >> 6) & 63);
-    ++size_;
-  }
-  void erase(int64_t i) {  // a member
-    if ((words_[i >> 6] &= ~(uint64_t{1} << (i & 63))) == 0) top_[i >> 12] &= ~(uint64_t{1} << ((i >> 6) & 63));
-    --size_;
-  }
-  int32_t lowest() const {  // of a set that is not empty
-    size_t t = 0;
-    while (top_[t] == 0) ++t;
-    const size_t w = 64 * t + static_cast<size_t>(__builtin_ctzll(top_[t]));
-    return static_cast<int32_t>(64 * w + static_cast<size_t>(__builtin_ctzll(words_[w])));
-  }
-  void clear() {
-    if (size_ != 0) resize(64 * static_cast<int64_t>(words_.size()));
-  }
-
- private:
-  std::vector<uint64_t> words_, top_;
-  int64_t size_ = 0;
-};
 
 class PoolIndex;
 

@@ -1,6 +1,8 @@
-"""The device blocks that a pool keeps (csrc/block_cache.h) on a model of a device runtime,
-built by g++ from tests/host/block_check.cpp: who may be given which block, when, and what
-happens when a call of the runtime fails (CPU only)."""
+"""Host-side parts that need no GPU, built by g++ and run on the CPU:
+- tests/host/block_check.cpp: the device blocks that a pool keeps (csrc/block_cache.h) on a
+  model of a device runtime: who may be given which block, when, and what happens when a call
+  of the runtime fails;
+- tests/host/id_set_check.cpp: the pool's set of free page ids (csrc/id_set.h)."""
 import os
 import shutil
 import subprocess
@@ -10,14 +12,16 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_kept_blocks(tmp_path):
+@pytest.mark.parametrize("name", ["block_check", "id_set_check"])
+def test_host_part(name, tmp_path):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
-    exe = os.path.join(str(tmp_path), "block_check")
-    r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I",
+    exe = os.path.join(str(tmp_path), name)
+    r = subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror", "-I",
                         os.path.join(ROOT, "paper_2511_02749_amd", "csrc"),
-                        os.path.join(ROOT, "tests", "host", "block_check.cpp"), "-o", exe], capture_output=True, text=True)
+                        os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    print(r.stdout, end="")
     assert r.returncode == 0, r.stderr[-4000:]
     assert "all checks passed" in r.stdout
