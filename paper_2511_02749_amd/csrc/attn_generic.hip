@@ -43,6 +43,7 @@
 
 #include "../../include/spanq.h"
 #include "dev_common.h"
+#include "grid.h"
 #include "kernels.h"
 #include "mfma_common.h"
 
@@ -322,12 +323,14 @@ hipError_t attn_generic_t(const PoolGeom& g, const WorkTile* tiles, int n, const
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_generic_kernel<D>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr != hipSuccess) return attr;
-  const int64_t items = static_cast<int64_t>(n) * kItemsPerTile * g.hq;
-  if (items * 64 * kGW >= (1ll << 32)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_generic_kernel<D>), dim3(static_cast<unsigned>(items)), dim3(64 * kGW), lds, s, tiles, kv,
-                     static_cast<const float*>(q), static_cast<float*>(out), static_cast<const float*>(g.base), g.layer_off,
-                     g.hq, g.hkv, scale_log2, rope, runs, static_cast<float*>(part_o), part_ml);
-  return hipGetLastError();
+  const int64_t items = static_cast<int64_t>(kItemsPerTile) * g.hq;  // of a tile
+  return launch_in_slices(n, items * 64 * kGW, hipErrorInvalidValue, [&](int64_t t0, int64_t nt) {
+    hipLaunchKernelGGL((attn_generic_kernel<D>), dim3(static_cast<unsigned>(nt * items)), dim3(64 * kGW), lds, s,
+                       tiles + t0, kv, static_cast<const float*>(q), static_cast<float*>(out),
+                       static_cast<const float*>(g.base), g.layer_off, g.hq, g.hkv, scale_log2, rope, runs,
+                       static_cast<float*>(part_o), part_ml);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace

@@ -40,6 +40,7 @@
 
 #include "../../include/spanq.h"
 #include "dev_common.h"
+#include "grid.h"
 #include "kernels.h"
 #include "mfma_common.h"
 
@@ -371,13 +372,14 @@ hipError_t launch_t(const PoolGeom& g, const WorkTile* tiles, int n, const TileR
   if (attr != hipSuccess) return attr;
   const int G = g.hq / g.hkv;
   const int chunks = split_chunks(G);
-  const int64_t items = static_cast<int64_t>(n) * g.hkv * chunks;
-  if (items * 64 * kSW >= (1ll << 32)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_split_kernel<D>), dim3(static_cast<unsigned>(items)), dim3(64 * kSW), lds, s, tiles, kt,
-                     static_cast<const bf16_t*>(q), static_cast<bf16_t*>(out), static_cast<const bf16_t*>(g.base),
-                     g.layer_off, g.hq, g.hkv, split_bm(G), chunks, scale_log2, rope, static_cast<f16_t*>(part_o),
-                     part_ml);
-  return hipGetLastError();
+  const int64_t items = static_cast<int64_t>(g.hkv) * chunks;  // of a tile
+  return launch_in_slices(n, items * 64 * kSW, hipErrorInvalidValue, [&](int64_t t0, int64_t nt) {
+    hipLaunchKernelGGL((attn_split_kernel<D>), dim3(static_cast<unsigned>(nt * items)), dim3(64 * kSW), lds, s,
+                       tiles + t0, kt, static_cast<const bf16_t*>(q), static_cast<bf16_t*>(out),
+                       static_cast<const bf16_t*>(g.base), g.layer_off, g.hq, g.hkv, split_bm(G), chunks, scale_log2,
+                       rope, static_cast<f16_t*>(part_o), part_ml);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace

@@ -2,6 +2,7 @@
 - tests/host/block_check.cpp: the device blocks that a pool keeps (csrc/block_cache.h) on a
   model of a device runtime: who may be given which block, when, and what happens when a call
   of the runtime fails;
+- tests/host/grid_check.cpp: launches over more row tiles than a grid takes (csrc/grid.h);
 - tests/host/id_set_check.cpp: the pool's set of free page ids (csrc/id_set.h)."""
 import os
 import shutil
@@ -12,7 +13,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("name", ["block_check", "id_set_check"])
+@pytest.mark.parametrize("name", ["block_check", "grid_check", "id_set_check"])
 def test_host_part(name, tmp_path):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
