@@ -206,7 +206,9 @@ __global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(2))) v
   // This wave's pages: wave, wave + kGW, .. of the list, or with `runs` a quarter of it in
   // one run, in either case up to the first that starts past the last row (positions do
   // not decrease along a list).  A step takes the page of pg, whose K is on its way, for
-  // row blocks X0 .. X1 - 1.
+  // row blocks X0 .. X1 - 1.  The planner's tiles start where a page does, or end with the one
+  // they start in: every row of a block sees some key of each page that the block takes, so
+  // that a page's infinite or NaN values (0 times them is NaN) reach no row before it.
   // Alternate pages keep the waves level on a causal list.  A cross list changes delta from
   // fragment to fragment, and each change costs a wave a trip to memory for its query: in
   // runs a wave meets a few of them, not one with every page (16 rows over 288 keys in

@@ -253,6 +253,8 @@ __global__ __launch_bounds__(64 * kSW) __attribute__((amdgpu_waves_per_eu(2, 2))
     float ts = 0.f;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {  // page 2kb + half: keys 16half .. of the block
+      const int key0 = 32 * kb + 16 * half;
+      if (key0 >= nk || pos0 + key0 > last_pos) break;  // no row sees it
       u32x4_t pw[kTerms];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -264,12 +266,29 @@ __global__ __launch_bounds__(64 * kSW) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int x = 0; x < kTerms; ++x) pw[x][e] = w[x];
       }
+      auto add = [&](int x, int db) {
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl[(half * D * 32 + db * 1024) / 16],
+                                                        __builtin_bit_cast(bf16x8_t, pw[x]), o[db], 0, 0, 0);
+      };
+      if (pos0 + key0 <= first_pos) {
 #pragma unroll
-      for (int x = kTerms - 1; x >= 0; --x)
+        for (int x = kTerms - 1; x >= 0; --x)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl[(half * D * 32 + db * 1024) / 16],
-                                                          __builtin_bit_cast(bf16x8_t, pw[x]), o[db], 0, 0, 0);
+          for (int db = 0; db < DB; ++db) add(x, db);
+      } else {
+        // Rows before the page keep their sums as they are: 0 times a value of the page that is
+        // infinite or NaN would end up in rows that do not see it.
+        const bool sees = qpos >= pos0 + key0;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          const f32x16_t before = o[db];
+#pragma unroll
+          for (int x = kTerms - 1; x >= 0; --x) add(x, db);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[db][i] = sees ? o[db][i] : before[i];
+          __builtin_amdgcn_sched_barrier(0);  // one block's copy at a time: no registers to spare
+        }
+      }
     }
     l += ts;
   };

@@ -976,8 +976,9 @@ int PoolIndex::decode(Plan* p, const std::vector<int32_t>& n_new, const std::vec
     const int32_t kv0 = static_cast<int32_t>(d.kv.size());
     append_query_keys(*p, ids, ps, t.pad4, d.kv);
     const int32_t kv1 = static_cast<int32_t>(d.kv.size());
-    for (int32_t j0 = 0; j0 < n; j0 += t.bm_cross) {
-      const int32_t nn = std::min(t.bm_cross, n - j0);
+    for (int32_t j0 = 0, nn = 0; j0 < n; j0 += nn) {
+      const int32_t at = (cur + j0) % ps;  // the first row's slot in its page
+      nn = std::min(t.rows_at_pages && at != 0 ? std::min(t.bm_cross, ps - at) : t.bm_cross, n - j0);
       const int32_t end = list_end(d.kv, kv0, kv1, pos_first + j0 + nn - 1, t.pad4);
       ct.push_back(CrossTile{static_cast<int32_t>(rows[q] + j0), nn, pos_first + j0, kv0, end});
       max_pages = std::max(max_pages, end - kv0);

@@ -62,6 +62,7 @@ struct Tiling {
   int target_items = 512;     // work-groups the cross launch aims for (KV splits x tiles x heads)
   int min_split_pages = 16;   // at least 256 keys per KV split
   bool pad4 = false;          // pad span runs to 4-page tiles and emit tile records
+  bool rows_at_pages = false; // decode rows that start inside a page: a tile up to the page's end first
   bool xcd_queues = false;    // order prefill tiles for the per-XCD queues (MFMA prefill kernel)
   int two_group_rows = 0;     // cross tiles of at most this many rows use kTwoKeyGroups
   int few_rows = 0;           // two-key-group tiles of at most this many rows go last
@@ -74,7 +75,10 @@ struct Tiling {
 // 8-wave work-group per CU walking (row tile, kv head) items: the cross launch aims
 // at one item per CU (splitting the keys further only adds partials to merge).
 // The generic kernel (fp32 pools: two work-groups of four waves per row tile and query
-// head) wants several work-groups per CU.
+// head) wants several work-groups per CU, and 16-row blocks that start where pages do: a row
+// block multiplies the values of every page that one of its rows sees into all of them, and 0
+// times an infinite or NaN value is NaN.  (Spans' rows and tiles start at pages anyway; a decode
+// step of several tokens may not, and gets a tile more.)
 // Few-row cross tiles (a short question over a long context) let the MFMA
 // kernel's two wave groups work on alternate key tiles; that needs four query
 // heads per kv head (two 32-row groups of four waves).
@@ -85,6 +89,7 @@ inline Tiling tiling_for(bool mfma, int bm, int hq, int hkv) {
   t.kv_heads = mfma ? hkv : hq;
   t.target_items = mfma ? 256 : 1024;
   t.pad4 = mfma;
+  t.rows_at_pages = !mfma;
   t.xcd_queues = mfma;
   t.two_group_rows = (mfma && hq == 4 * hkv) ? 32 : 0;
   t.few_rows = t.two_group_rows > 0 ? 16 : 0;
