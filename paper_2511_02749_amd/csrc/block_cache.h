@@ -54,8 +54,10 @@ class BlockCache {
   // else a stream-ordered allocation (always that in a stream under capture, which cannot
   // wait for an event from outside).  If that fails, what the caches of the device keep is
   // freed, this one's and other pools', and it is tried once more: keeping blocks makes no call
-  // fail that passes without.
+  // fail that passes without.  0 bytes: no block, whatever is kept.
   Error take(size_t bytes, Stream s, DevBlock* out) {
+    *out = DevBlock{};
+    if (bytes == 0) return Error{};
     const typename Rt::Device scope(device_);
     const bool captured = Rt::capturing(s);
     if (!captured && take_kept(bytes, s, out)) return Error{};
@@ -63,7 +65,7 @@ class BlockCache {
     void* p = nullptr;
     Error e = Rt::alloc(&p, got, s);
     if (e != Error{} && !captured && free_all_kept(s)) e = Rt::alloc(&p, got, s);
-    *out = e == Error{} ? DevBlock{p, got, !captured} : DevBlock{};
+    if (e == Error{}) *out = DevBlock{p, got, !captured};
     return e;
   }
 

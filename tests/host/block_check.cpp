@@ -196,6 +196,19 @@ void capture() {
   c.clear(&a);
 }
 
+// 0 bytes (a decode step without tokens) are no block, whether or not one is kept.
+void nothing() {
+  Cache c(0);
+  StreamModel s;
+  DevBlock x;
+  CHECK(c.take(0, &s, &x) == 0 && x.p == nullptr);
+  c.give(take(c, 70000, s), &s);
+  x = DevBlock{&c, 1, true};
+  CHECK(c.take(0, &s, &x) == 0 && x.p == nullptr);
+  c.give(x, &s);
+  c.clear(&s);
+}
+
 // Near the memory limit an allocation passes that would pass if nothing were kept, whichever
 // pool of the device keeps it; one that is too large fails, and leaves nothing in use.
 void limit() {
@@ -268,6 +281,7 @@ int main() {
   independent_streams();
   bounds();
   capture();
+  nothing();
   limit();
   devices();
   refused_record();

@@ -5,6 +5,7 @@ import dataclasses
 
 import pytest
 
+import paper_2511_02749_amd as spanq
 import workloads as W
 from tests.helpers import GpuRun
 
@@ -59,3 +60,24 @@ def test_blocks_pass_between_plans_of_two_streams(dtype):
     for run in runs:
         run.close()
 
+
+
+@pytest.mark.parametrize("kept", [False, True])
+def test_step_without_tokens_is_no_step(kept):
+    """span_decode_attend after a decode step in which no query had a token: refused, whether or
+    not the pool keeps a block from an earlier plan."""
+    _need_gpu()
+    wl = W.small_workload(n_queries=2)
+    run = GpuRun(wl)
+    if kept:
+        run.run_batch(wl.batches[0]).destroy()
+    plan = run.pool.plan(wl.batches[0])
+    if kept:
+        run.pool.plan(wl.batches[0][:1]).destroy()
+    torch.cuda.synchronize()
+    plan.decode([0] * len(wl.batches[0]), [0] * len(wl.batches[0]))
+    with pytest.raises(spanq.SpanError) as ei:
+        plan.decode_attend(0, run.q, run.k, run.v, run.out)
+    assert ei.value.code == -4
+    plan.destroy()
+    run.close()
