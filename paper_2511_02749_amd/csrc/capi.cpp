@@ -68,8 +68,6 @@ int max_parts(const std::vector<CombineTile>& c) {
   return m;
 }
 
-Tiling plan_tiling(const span_plan_t* pl);
-
 // The (m, l) half of a split-KV partial buffer, after its part_o_elems O elements.
 float* part_ml_of(const span_pool* p, float* part, size_t part_o_elems) {
   if (!part) return nullptr;
@@ -727,11 +725,13 @@ int span_prefill_fragments(span_plan_t* pl, int32_t layer, const void* q, const 
   const int nt = static_cast<int>(P.t_prefill.size());
   unsigned* sched = pl->sched + kSchedWords * (pl->sched_next++ % span_plan_t::kSchedSlots);
   const int nch = P.prefill_chunks.empty() ? 0 : static_cast<int>(P.prefill_chunks.size()) - 1;
-  e = pl->mfma ? launch_prefill_mfma(g, pl->tp, nt, pl->kt, q, out, pl->rope, sched, P.prefill_chunks.data(),
-                                     pl->xch, nch, &pl->prefill_queues, s)
-      : pl->split
-          ? launch_attn_split(g, pl->tp, nt, pl->kt, q, out, nullptr, nullptr, pl->rope, s)
-               : launch_attn_generic(g, pl->tp, nt, pl->kv, q, out, nullptr, nullptr, pl->rope, false, s);
+  if (pl->mfma)
+    e = launch_prefill_mfma(g, pl->tp, nt, pl->kt, q, out, pl->rope, sched, P.prefill_chunks.data(), pl->xch, nch,
+                            &pl->prefill_queues, s);
+  else if (pl->split)
+    e = launch_attn_split(g, pl->tp, nt, pl->kt, q, out, nullptr, nullptr, pl->rope, s);
+  else
+    e = launch_attn_generic(g, pl->tp, nt, pl->kv, q, out, nullptr, nullptr, pl->rope, false, s);
   if (e != hipSuccess) return hip_fail(e, "span_prefill_fragments: attention");
   tm.mark(2);
   if (!tm.ev.empty()) pl->ev_prefill.push_back(tm.ev);

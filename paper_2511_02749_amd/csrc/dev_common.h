@@ -1,4 +1,4 @@
-// Device helpers shared by the HIP kernels: bf16 storage and rotary angles.
+// Device helpers shared by the HIP kernels: bf16 storage, split-KV partials, the slot order of V.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -50,15 +50,5 @@ struct PartOf<float> {
 // swapped, i.e. quads ordered {0-3, 8-11, 4-7, 12-15}.  A P.V operand of the MFMA
 // kernel then covers 8 consecutive positions (one 16-byte LDS read).
 __host__ __device__ __forceinline__ int v_pos(int s) { return (s & 3) | ((s & 4) << 1) | ((s & 8) >> 1); }
-
-// cos and sin of position `pos` at frequency index i (rotary pair (i, i + d/2)),
-// read from the pool's table of (cos, sin) pairs laid out [position][d/2]; the
-// table is computed on the host in double precision and rounded once.
-__device__ __forceinline__ void rope_cs(const float2* __restrict__ tab, int half, int pos, int i, float* sn,
-                                        float* cs) {
-  const float2 v = tab[static_cast<int64_t>(pos) * half + i];
-  *cs = v.x;
-  *sn = v.y;
-}
 
 }  // namespace spanq

@@ -1,5 +1,5 @@
-// Launchers of the HIP kernels (kernels.hip, attn_mfma.hip, few_mfma.hip, prefill_mfma.hip,
-// probes.hip).
+// Launchers of the HIP kernels (kernels.hip, attn_generic.hip, attn_split.hip, attn_mfma.hip,
+// few_mfma.hip, prefill_mfma.hip, probes.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -30,8 +30,8 @@ hipError_t launch_append_kv(const PoolGeom& g, const SlotWrite* writes, int n_wr
 hipError_t launch_move_pages(const PoolGeom& g, const MovePage* moves, int n_moves, const float2* rope,
                              hipStream_t s);
 
-// Generic span attention (any dtype, any heads per kv head) over work tiles of up to
-// kGenericBM rows.
+// Span attention on fp32 pools, any number of query heads per kv head, over work tiles of up
+// to kGenericBM rows; key lists page by page.
 constexpr int kGenericBM = 64;
 // runs: give each wave its pages in one run of a list (cross and decode lists, whose
 // reposition delta changes along them) and not every few pages (causal prefill lists).

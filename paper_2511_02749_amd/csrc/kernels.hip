@@ -369,7 +369,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineTile* __restr
         for (int i = 0; i < 8; ++i) x.a[i] *= f;
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
-          if (ml[u].x == -INFINITY) continue;  // (its row was not written)
+          if (ml[u].x == -INFINITY) continue;  // no key of the row, or past the last part (v[u] not loaded)
           const float g = exp2f(ml[u].x - mn), lg = ml[u].y * g;
           x.l += lg;
 #pragma unroll
