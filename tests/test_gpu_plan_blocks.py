@@ -1,6 +1,11 @@
 """Device blocks that a pool keeps from destroyed plans and finished decode steps for the
-next ones: plans of very different sizes, made and destroyed in turn on two streams with
-no synchronisation between them, give the outputs that each gives on a pool of its own."""
+next ones:
+- plans of very different sizes, made and destroyed in turn on two streams, each pool's in the
+  order of its pages, give the outputs that each gives on a pool of its own;
+- a plan whose pages have nothing to do with those of a destroyed plan that still waits to
+  run on another stream leaves that plan's block alone, with no order between them but the
+  block's own;
+- a decode step takes no block that the step before it still waits to read."""
 import dataclasses
 
 import pytest
@@ -8,6 +13,7 @@ import pytest
 import paper_2511_02749_amd as spanq
 import workloads as W
 from tests.helpers import GpuRun
+from tests.test_decode import _cut
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -60,6 +66,94 @@ def test_blocks_pass_between_plans_of_two_streams(dtype):
     for run in runs:
         run.close()
 
+
+
+def _busy(stream, ms=60):
+    """Work for some tens of ms on the stream (a product of 8192 takes about 1 ms)."""
+    with torch.cuda.stream(stream):
+        a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+        for _ in range(ms):
+            a @ a
+        return stream.record_event()
+
+
+def _pages(plan, batch):
+    return {p for i, q in enumerate(batch) for s in range(-1, len(q.frags) + 1) for p in plan.block_table(i, s)[0]}
+
+
+@pytest.mark.parametrize("dtype,hq", [("bf16", 8), ("bf16", 6), ("f32", 4)])
+def test_a_block_waits_for_its_last_reader(dtype, hq):
+    _need_gpu()
+    wl = W.small_workload(dtype=dtype, n_q_heads=hq, n_kv_heads=2, prefix_len=40, frag_lens=(300, 129, 90, 290, 120, 100),
+                          frags_per_query=3, n_queries=2, cross_len=40, orders=[[0, 1, 2], [3, 4, 5]])
+    first, second = wl.batches[0][:1], wl.batches[0][1:]
+    empty = W.Span(tokens=first[0].cross.tokens[:0], row=first[0].cross.row)
+    prefix = [W.Query(prefix=first[0].prefix, frags=[], cross=empty)]
+    holder = [W.Query(prefix=first[0].prefix, frags=[], cross=first[0].cross)]
+
+    def layer(run, plan, out, stream=None):
+        plan.prefill(0, run.q, run.k, run.v, out, stream=stream)
+        plan.cross(0, run.q, run.k, run.v, out, stream=stream)
+
+    want = []
+    for batch in (first, second):
+        run = GpuRun(wl)
+        run.run_batch(prefix)
+        out = torch.zeros_like(run.out)
+        plan = run.pool.plan(batch)
+        layer(run, plan, out)
+        torch.cuda.synchronize()
+        want.append(out)
+        plan.destroy()
+        run.close()
+    run = GpuRun(wl)
+    run.run_batch(prefix).destroy()  # both queries find the prefix cached
+    made, works, other = (torch.cuda.Stream() for _ in range(3))
+    outs = [torch.zeros_like(run.out) for _ in range(2)]
+    torch.cuda.synchronize()
+    plan = run.pool.plan(first, made)
+    used = _pages(plan, first)
+    busy = _busy(works)
+    layer(run, plan, outs[0], works)
+    plan.commit()
+    hold = run.pool.plan(holder, other)  # takes the cross pages that the commit freed
+    plan.destroy()
+    plan = run.pool.plan(second, other)
+    assert used & _pages(plan, second) == set(plan.block_table(0, -1)[0])  # the prefix's, and no others
+    layer(run, plan, outs[1], other)
+    assert not busy.query()  # the first plan's kernels had not begun
+    torch.cuda.synchronize()
+    for got, ref in zip(outs, want):
+        assert torch.equal(got, ref)
+    plan.destroy()
+    hold.destroy()
+    run.close()
+
+
+@pytest.mark.parametrize("dtype,hq", [("bf16", 8), ("bf16", 6), ("f32", 4)])
+def test_a_decode_step_waits_for_the_one_before(dtype, hq):
+    _need_gpu()
+    wl = W.small_workload(dtype=dtype, n_q_heads=hq, n_kv_heads=2, n_queries=2, cross_len=40)
+    full = wl.batches[0]
+
+    def decode(made, works):
+        run = GpuRun(wl)
+        plan = run.pool.plan([_cut(q, 10) for q in full], made)
+        plan.prefill(0, run.q, run.k, run.v, run.out)
+        plan.cross(0, run.q, run.k, run.v, run.out)
+        torch.cuda.synchronize()
+        _busy(works)
+        for step in range(10, 14):
+            plan.decode([1] * len(full), [q.cross.row + step for q in full], made)
+            plan.decode_attend(0, run.q, run.k, run.v, run.out, stream=works)
+        torch.cuda.synchronize()
+        out = run.out.clone()
+        plan.destroy()
+        run.close()
+        return out
+
+    stream = torch.cuda.Stream()
+    assert torch.equal(decode(torch.cuda.Stream(), torch.cuda.Stream()), decode(stream, stream))
 
 
 @pytest.mark.parametrize("kept", [False, True])
