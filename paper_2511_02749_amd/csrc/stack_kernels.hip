@@ -242,14 +242,17 @@ __global__ __launch_bounds__(kArgThreads) void argmax_rows_kernel(const float* _
 //
 // Bound: HBM (W read once; slices x 4 bytes of partials per output element).  Against one
 // 2-byte load of X per weight row and M, and a reduction over 32 row groups in LDS, both
-// passes from the last-level cache, us before -> now at 4 rows: 2048 x 16384 22.3 -> 17,
-// 2048 x 32000 38.9 -> 29 (59 -> 29 as the LM head, whose work-groups of 2048 columns
-// filled half the chip), 8192 x 2048 13.1 -> 11.2, 2048 x 3072 7.6 -> 8.0; at 8 rows
-// 43 -> 23, 75.8 -> 36, 16.2 -> 15.7, 12.0 -> 9.6; at 1 row the same to 7%.
-// Slices (gemv_slices): about four work-groups per CU, but 128 to 512 rows of K each and
-// at most 16 unless that makes them longer: shorter ones spend their time in the
-// reduction, and pass 2, whose one work-group per row reads every slice, grows (64-row
-// slices: 8.0 -> 11.1 us at 2048 x 3072, 4 rows).
+// passes from the last-level cache, us before -> now at 4 rows (K x N): 2048 x 16384 22.5 -> 17.1,
+// 2048 x 32000 39.3 -> 29.4 (59 -> 29 as the LM head, whose work-groups of 2048 columns
+// filled half the chip), 8192 x 2048 13.2 -> 11.4, 2048 x 3072 7.7 -> 7.1; at 8 rows
+// 42.9 -> 22.9, 75.4 -> 35.5, 16.7 -> 16.0, 12.3 -> 9.1; at 1 row 15.6 -> 14.4, 24.8 -> 23.5,
+// 8.8 -> 8.2, 5.9 -> 5.8.  (Up to 0.8 us slower at 4 and 8 rows below 512 x 512, and 2% at 1 row
+// of 4096 x 4096 and 14336 x 4096.)
+// Slices (gemv_slices): eight, of at least 64 rows of K, are enough to fill the chip and cheap to
+// add up; more, of at least 256 rows, where there are few column blocks.  2048 x 3072 at 1, 4 and
+// 8 rows: 5.8, 7.1, 9.1 us with 8 slices, 6.3, 7.9, 9.8 with 16; 4096 x 4096 at 8 rows: 14.5 with
+// 8, 13.6 with 16; 4096 x 12288: 25.8 with 8, 32.0 with 11; 256 x 256: 6.5 with 4, 7.0 with 2.
+// Fewer than eight where the blocks alone are four per CU, and as many as 512 rows each take.
 // Column blocks: 128 columns read longer segments and reduce less, 64 give twice the
 // work-groups.  The line is two work-groups of 128 columns per CU: 8192 x 2048 (256) takes
 // 13.8 us with 128 columns and 11.2 with 64, 4096 x 4096 (512) 10.3 and 11.5.
@@ -504,7 +507,8 @@ namespace {
 // K slices of the GEMV's first pass and rows per slice (a multiple of 16).
 int gemv_slices(int N, int K, int* rows) {
   const int blocks = (N + 127) / 128;
-  int s = std::min({(1024 + blocks - 1) / blocks, std::max(1, K / 128), 16});
+  int s = std::max(std::min(K / 64, 8), std::min(K / 256, 768 / blocks));
+  s = std::max(1, std::min({s, (1024 + blocks - 1) / blocks, 16}));
   s = std::max(s, (K + kGemvMaxRows - 1) / kGemvMaxRows);
   *rows = ((K + s - 1) / s + 15) / 16 * 16;
   return (K + *rows - 1) / *rows;
