@@ -1,5 +1,7 @@
 // Span attention on fp32 pools for gfx950, any number of query heads per kv head, on fp32
-// matrix instructions (v_mfma_f32_16x16x4_f32).
+// matrix instructions (v_mfma_f32_16x16x4_f32).  On bf16 pools too, each element widened as it
+// is loaded: for plans whose work lists for the split-precision kernel, which is twice as fast
+// (attn_split.hip), do not fit the memory they must go to.
 //
 // One work-group of four waves per (32 rows of a row tile, query head); the planner's row
 // tiles hold up to 64 rows, two items.  Every wave holds all 32 rows, as two 16-row blocks
@@ -61,6 +63,27 @@ constexpr int kItemsPerTile = kGenericBM / kItemRows;
 // Four consecutive elements of a caller's row, whose base is only known to be aligned to
 // an element.
 typedef float row4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef bf16_t row4h_t __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ row4_t load_row4(const float* p) { return *reinterpret_cast<const row4_t*>(p); }
+__device__ __forceinline__ row4_t load_row4(const bf16_t* p) {
+  const row4h_t v = *reinterpret_cast<const row4h_t*>(p);
+  return row4_t{to_f32(v[0]), to_f32(v[1]), to_f32(v[2]), to_f32(v[3])};
+}
+__device__ __forceinline__ void store_row4(float* p, const row4_t& w) { *reinterpret_cast<row4_t*>(p) = w; }
+__device__ __forceinline__ void store_row4(bf16_t* p, const row4_t& w) {
+  *reinterpret_cast<row4h_t*>(p) = row4h_t{f32_to_bf16(w[0]), f32_to_bf16(w[1]), f32_to_bf16(w[2]), f32_to_bf16(w[3])};
+}
+// The same of a page (aligned to four elements), and of a partial.
+__device__ __forceinline__ f32x4_t load_page4(const float* p) { return *reinterpret_cast<const f32x4_t*>(p); }
+__device__ __forceinline__ f32x4_t load_page4(const bf16_t* p) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  return f32x4_t{lo_bf16(v.x), hi_bf16(v.x), lo_bf16(v.y), hi_bf16(v.y)};
+}
+__device__ __forceinline__ void store_part4(float* p, const f32x4_t& w) { *reinterpret_cast<f32x4_t*>(p) = w; }
+__device__ __forceinline__ void store_part4(f16_t* p, const f32x4_t& w) {
+  *reinterpret_cast<f16x4_t*>(p) =
+      f16x4_t{static_cast<f16_t>(w[0]), static_cast<f16_t>(w[1]), static_cast<f16_t>(w[2]), static_cast<f16_t>(w[3])};
+}
 
 template <int D>
 struct GGeo {
@@ -68,11 +91,11 @@ struct GGeo {
   static constexpr int LDS = kGW * kItemRows * (OROW + 2) * 4;
 };
 
-template <int D>
+template <typename T, int D>
 __global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(2))) void attn_generic_kernel(
-    const WorkTile* __restrict__ tiles, const KvPage* __restrict__ kv, const float* __restrict__ q, float* __restrict__ out,
-    const float* __restrict__ pool, int64_t layer_off, int hq, int hkv, float scale_log2, const float2* __restrict__ rope,
-    bool runs, float* __restrict__ part_o, float* __restrict__ part_ml) {
+    const WorkTile* __restrict__ tiles, const KvPage* __restrict__ kv, const T* __restrict__ q, T* __restrict__ out,
+    const T* __restrict__ pool, int64_t layer_off, int hq, int hkv, float scale_log2, const float2* __restrict__ rope,
+    bool runs, typename PartOf<T>::type* __restrict__ part_o, float* __restrict__ part_ml) {
   constexpr int H = D / 2;
   constexpr int NT = D / 16;  // 16-dim steps of the scores, 16-dim blocks of the output
   constexpr int OROW = GGeo<D>::OROW;
@@ -96,9 +119,9 @@ __global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(2))) v
   const bool two = t.n_rows > 16;  // both row blocks hold rows
   const int last_pos = t.q_pos0 + t.n_rows - 1;
   const int64_t page_elems = 2ll * hkv * kPage * D;
-  const float* const kbase = pool + layer_off + static_cast<int64_t>(kvh) * kPage * D + r * D + 4 * g;
+  const T* const kbase = pool + layer_off + static_cast<int64_t>(kvh) * kPage * D + r * D + 4 * g;
   // slots 4g .. 4g + 3 are quad (g & 1) << 1 | g >> 1 of a V row
-  const float* const vbase = pool + layer_off + static_cast<int64_t>(hkv + kvh) * kPage * D + r * kPage +
+  const T* const vbase = pool + layer_off + static_cast<int64_t>(hkv + kvh) * kPage * D + r * kPage +
                          4 * (((g & 1) << 1) | (g >> 1));
 
   f32x4_t o[kRB][NT];
@@ -115,14 +138,14 @@ __global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(2))) v
 
   f32x4_t kr[NT], vr[NT];
   auto load_k = [&](int pid) {
-    const float* p = kbase + static_cast<int64_t>(pid) * page_elems;
+    const T* p = kbase + static_cast<int64_t>(pid) * page_elems;
 #pragma unroll
-    for (int b = 0; b < NT; ++b) kr[b] = *reinterpret_cast<const f32x4_t*>(p + 16 * b);
+    for (int b = 0; b < NT; ++b) kr[b] = load_page4(p + 16 * b);
   };
   auto load_v = [&](int pid) {
-    const float* p = vbase + static_cast<int64_t>(pid) * page_elems;
+    const T* p = vbase + static_cast<int64_t>(pid) * page_elems;
 #pragma unroll
-    for (int b = 0; b < NT; ++b) vr[b] = *reinterpret_cast<const f32x4_t*>(p + 16 * b * kPage);
+    for (int b = 0; b < NT; ++b) vr[b] = load_page4(p + 16 * b * kPage);
   };
   // qv <- R(position - delta) q; positions below the table's start do not occur (a key's
   // stored position is its final one less delta, and no row reads past its own position)
@@ -135,12 +158,12 @@ __global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int i = 0; i < 4; ++i) qv[x][b][i] = 0.f;
       return;
     }
-    const float* src = q + (static_cast<int64_t>(t.q_row0 + row) * hq + h) * D + 4 * g;
+    const T* src = q + (static_cast<int64_t>(t.q_row0 + row) * hq + h) * D + 4 * g;
     const float2* tab = rope + static_cast<int64_t>(t.q_pos0 + row - delta) * H + 4 * g;
 #pragma unroll
     for (int b = 0; b < NT / 2; ++b) {
-      const row4_t y0 = *reinterpret_cast<const row4_t*>(src + 16 * b);
-      const row4_t y1 = *reinterpret_cast<const row4_t*>(src + 16 * b + H);
+      const row4_t y0 = load_row4(src + 16 * b);
+      const row4_t y1 = load_row4(src + 16 * b + H);
       const float4 c01 = *reinterpret_cast<const float4*>(tab + 16 * b);
       const float4 c23 = *reinterpret_cast<const float4*>(tab + 16 * b + 2);
       const float cs[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
@@ -300,15 +323,18 @@ __global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
       for (int j = 0; j < 4; ++j) a[j] += v[j] * f;
     }
+    const float inv = ll > 0.f ? 1.f / ll : 0.f;
     if (t.part < 0) {
-      const float inv = ll > 0.f ? 1.f / ll : 0.f;
       row4_t w;
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[j] = a[j] * inv;
-      *reinterpret_cast<row4_t*>(out + (static_cast<int64_t>(t.q_row0 + x) * hq + h) * D + 4 * c) = w;
+      store_row4(out + (static_cast<int64_t>(t.q_row0 + x) * hq + h) * D + 4 * c, w);
     } else {
       const int64_t slot = (static_cast<int64_t>(t.part) * hq + h) * kGenericBM + row0 + x;
-      *reinterpret_cast<f32x4_t*>(part_o + slot * D + 4 * c) = a;
+      if constexpr (PartOf<T>::normalized)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] *= inv;
+      store_part4(part_o + slot * D + 4 * c, a);
       if (c == 0) {
         part_ml[slot * 2] = mm;
         part_ml[slot * 2 + 1] = ll;
@@ -317,20 +343,20 @@ __global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 }
 
-template <int D>
+template <typename T, int D>
 hipError_t attn_generic_t(const PoolGeom& g, const WorkTile* tiles, int n, const KvPage* kv, const void* q, void* out,
                           void* part_o, float* part_ml, const float2* rope, bool runs, hipStream_t s) {
   const float scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
   constexpr int lds = GGeo<D>::LDS;
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_generic_kernel<D>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_generic_kernel<T, D>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr != hipSuccess) return attr;
   const int64_t items = static_cast<int64_t>(kItemsPerTile) * g.hq;  // of a tile
   return launch_in_slices(n, items * 64 * kGW, hipErrorInvalidValue, [&](int64_t t0, int64_t nt) {
-    hipLaunchKernelGGL((attn_generic_kernel<D>), dim3(static_cast<unsigned>(nt * items)), dim3(64 * kGW), lds, s,
-                       tiles + t0, kv, static_cast<const float*>(q), static_cast<float*>(out),
-                       static_cast<const float*>(g.base), g.layer_off, g.hq, g.hkv, scale_log2, rope, runs,
-                       static_cast<float*>(part_o), part_ml);
+    hipLaunchKernelGGL((attn_generic_kernel<T, D>), dim3(static_cast<unsigned>(nt * items)), dim3(64 * kGW), lds, s,
+                       tiles + t0, kv, static_cast<const T*>(q), static_cast<T*>(out), static_cast<const T*>(g.base),
+                       g.layer_off, g.hq, g.hkv, scale_log2, rope, runs,
+                       static_cast<typename PartOf<T>::type*>(part_o), part_ml);
     return hipGetLastError();
   });
 }
@@ -340,9 +366,12 @@ hipError_t attn_generic_t(const PoolGeom& g, const WorkTile* tiles, int n, const
 hipError_t launch_attn_generic(const PoolGeom& g, const WorkTile* tiles, int n, const KvPage* kv, const void* q,
                                void* out, void* part_o, float* part_ml, const float2* rope, bool runs, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  if (g.dtype != SPAN_F32) return hipErrorInvalidValue;
-  return g.d == 128 ? attn_generic_t<128>(g, tiles, n, kv, q, out, part_o, part_ml, rope, runs, s)
-                    : attn_generic_t<64>(g, tiles, n, kv, q, out, part_o, part_ml, rope, runs, s);
+  auto go = [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    return g.dtype == SPAN_BF16 ? attn_generic_t<bf16_t, D>(g, tiles, n, kv, q, out, part_o, part_ml, rope, runs, s)
+                                : attn_generic_t<float, D>(g, tiles, n, kv, q, out, part_o, part_ml, rope, runs, s);
+  };
+  return g.d == 128 ? go(std::integral_constant<int, 128>{}) : go(std::integral_constant<int, 64>{});
 }
 
 }  // namespace spanq

@@ -341,16 +341,37 @@ int spanq::plan_impl(span_pool* pool, const span_query* qs, int32_t nq, void* st
     }
     pl->rope = pool->rope_tab;
     auto& hb = pl->host_meta;
-    // the generic kernel reads key lists page by page, the others in tile records
-    size_t o_kv = pl->mfma || pl->split ? 0 : put(hb, P.kv), o_kt = put(hb, P.kv_tiles), o_k3p = put(hb, P.k3_prefill),
-           o_k3c = put(hb, P.k3_cross);
-    size_t o_tp = put(hb, P.t_prefill), o_tc = put(hb, P.t_cross), o_cb = put(hb, P.combine),
-           o_mv = put(hb, P.moves);
-    size_t o_sc = put(hb, std::vector<unsigned>(kSchedWords * span_plan_t::kSchedSlots, 0u));
-    size_t o_xc = put(hb, P.prefill_chunks);
-    pl->part_o_elems = static_cast<size_t>(P.n_parts) * pool->cfg.num_q_heads * pl->bm * d;
-    const size_t part_bytes = pl->part_o_elems * part_elem_bytes(pool->cfg.dtype == SPAN_BF16) +
-                              static_cast<size_t>(P.n_parts) * pool->cfg.num_q_heads * pl->bm * 2 * sizeof(float);
+    size_t o_kv, o_kt, o_k3p, o_k3c, o_tp, o_tc, o_cb, o_mv, o_sc, o_xc, part_bytes;
+    auto lay_out = [&] {
+      hb.clear();
+      // the generic kernel reads key lists page by page, the others in tile records
+      o_kv = pl->mfma || pl->split ? 0 : put(hb, P.kv);
+      o_kt = put(hb, P.kv_tiles);
+      o_k3p = put(hb, P.k3_prefill);
+      o_k3c = put(hb, P.k3_cross);
+      o_tp = put(hb, P.t_prefill);
+      o_tc = put(hb, P.t_cross);
+      o_cb = put(hb, P.combine);
+      o_mv = put(hb, P.moves);
+      o_sc = put(hb, std::vector<unsigned>(kSchedWords * span_plan_t::kSchedSlots, 0u));
+      o_xc = put(hb, P.prefill_chunks);
+      pl->part_o_elems = static_cast<size_t>(P.n_parts) * pool->cfg.num_q_heads * pl->bm * d;
+      part_bytes = pl->part_o_elems * part_elem_bytes(pool->cfg.dtype == SPAN_BF16) +
+                   static_cast<size_t>(P.n_parts) * pool->cfg.num_q_heads * pl->bm * 2 * sizeof(float);
+      return ((hb.size() + 255) & ~static_cast<size_t>(255)) + part_bytes;
+    };
+    if (lay_out() > region_bytes && region && pl->split) {
+      // The split-precision kernel's lists, a tile per 128 / g tokens of a row and a record per
+      // 64 keys of a span, can be larger than the generic kernel's, 64 tokens a tile and 16
+      // bytes a page (1.4 times with one-page spans, 13 times with 130 heads per kv head): where
+      // only the latter fit, the generic kernel takes the plan.
+      pl->split = false;
+      pl->bm = kGenericBM;
+      t = plan_tiling(pl);
+      t.materialize = (pool->cfg.flags & SPAN_FLAG_MATERIALIZE) != 0;
+      pool->index->rebuild_work(&P, t);
+      lay_out();
+    }
     if (region) {
       const size_t meta_bytes = (hb.size() + 255) & ~static_cast<size_t>(255);
       if (meta_bytes + part_bytes > region_bytes) {

@@ -917,6 +917,20 @@ void PoolIndex::build_work(Plan* p, const Tiling& t) {
   tile_records(p->kv, t.pad4, &p->kv_tiles);
 }
 
+void PoolIndex::rebuild_work(Plan* p, const Tiling& t) {
+  p->kv.clear();
+  p->k3_prefill.clear();
+  p->k3_cross.clear();
+  p->t_prefill.clear();
+  p->t_cross.clear();
+  p->combine.clear();
+  p->rows_prefill.clear();
+  p->rows_cross.clear();
+  p->n_parts = 0;
+  p->prefill_pairs = p->cross_pairs = p->cross_kv_pages = 0;
+  build_work(p, t);
+}
+
 int PoolIndex::decode(Plan* p, const std::vector<int32_t>& n_new, const std::vector<int64_t>& rows,
                       const Tiling& t, std::string* msg) {
   const int32_t ps = page_size_;

@@ -164,6 +164,8 @@ class PoolIndex {
   // Returns 0, or -2 (pool full, unchanged), -1 (bad input) with msg set.
   int plan(const std::vector<QueryIn>& qs, bool build_work, const Tiling& tiling, Plan* out,
            std::string* msg);
+  // The plan's work lists again, for another tiling.
+  void rebuild_work(Plan* p, const Tiling& tiling);
   // Append n_new[q] decoded tokens (caller rows rows[q] ..) to each query's cross
   // segment: pages for them (transient, like cross pages) and the decode step's
   // work lists in p->dec.  Returns 0, -2 (pool full; plan and pool unchanged) or -1.

@@ -114,6 +114,26 @@ void run(uint64_t seed, int steps) {
     CHECK(rc[0] == rc[1] && rc[0] == rc[2], "one pool refuses what another takes");
     if (rc[0]) continue;
     ++plans;
+    {  // lists made again for another tiling are those of a plan made for it
+      Plan again = P[1];
+      pools[1].rebuild_work(&again, t[2]);
+      auto bytes = [](const Plan& p) {
+        std::string out;
+        auto add = [&](const auto& v) {
+          out.append(std::to_string(v.size()));
+          if (!v.empty()) out.append(reinterpret_cast<const char*>(v.data()), v.size() * sizeof(v[0]));
+        };
+        add(p.kv), add(p.kv_tiles), add(p.k3_prefill), add(p.k3_cross), add(p.t_prefill), add(p.t_cross);
+        add(p.prefill_chunks), add(p.combine);
+        for (const auto* runs : {&p.rows_prefill, &p.rows_cross})
+          for (const auto& r : *runs) out += " " + std::to_string(r.row0) + "+" + std::to_string(r.n);
+        for (int64_t v : {int64_t{p.n_parts}, int64_t{p.n_cross_few}, int64_t{p.kv_splits}, int64_t{p.max_pos},
+                          int64_t{p.bm_cross}, p.prefill_pairs, p.cross_pairs, p.cross_kv_pages})
+          out += " " + std::to_string(v);
+        return out;
+      };
+      CHECK(bytes(again) == bytes(P[2]), "rebuilt work lists differ");
+    }
     auto compare = [&](auto tiles, auto kv, auto kt, int32_t Tiling::*bm, const char* what) {
       const Seen want = rows_see(tiles(P[0]), kv(P[0]), kt(P[0]), t[0], ps, t[0].*bm);
       for (int i = 1; i < 3; ++i) {
