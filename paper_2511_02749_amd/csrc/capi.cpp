@@ -45,7 +45,8 @@ struct span_pool {
   void* dev = nullptr;
   bool owns_dev = false;
   // the attention kernels of this pool: the bf16 MFMA ones, else on bf16 pools the
-  // split-precision one, else (fp32 pools) the generic one
+  // split-precision one (or the generic one, for a span_plan_static that only fits in its form),
+  // on fp32 pools the generic one
   bool use_mfma = false;
   std::set<span_plan_t*> plans;
   std::vector<hipEvent_t> event_cache;  // reusable timing events

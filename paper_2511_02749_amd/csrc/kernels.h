@@ -30,8 +30,9 @@ hipError_t launch_append_kv(const PoolGeom& g, const SlotWrite* writes, int n_wr
 hipError_t launch_move_pages(const PoolGeom& g, const MovePage* moves, int n_moves, const float2* rope,
                              hipStream_t s);
 
-// Span attention on fp32 pools, any number of query heads per kv head, over work tiles of up
-// to kGenericBM rows; key lists page by page.
+// Span attention at fp32 precision, any number of query heads per kv head, over work tiles of up
+// to kGenericBM rows; key lists page by page.  For fp32 pools, and bf16 pools' plans whose lists
+// must be small.
 constexpr int kGenericBM = 64;
 // runs: give each wave its pages in one run of a list (cross and decode lists, whose
 // reposition delta changes along them) and not every few pages (causal prefill lists).
